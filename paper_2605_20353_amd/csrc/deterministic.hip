@@ -3,7 +3,7 @@
 // samples, model, tile and device.  The default scatters add floats in an
 // order that depends on timing (atomics, LDS compare-and-swap, per-workgroup
 // flushes); here every sum has a fixed order:
-//   1. the sampling kernel (k_loss_grad, SRC = 2) writes the sampled tensor
+//   1. the sampling kernel (k_loss_grad, src = 2) writes the sampled tensor
 //      -- coordinates and y = w f'(x, m) of every sample -- and each
 //      wavefront's partial objective into its own slot;
 //   2. k_det_pairs lists (model row, sample) for every sample and mode;
@@ -157,12 +157,22 @@ __global__ void __launch_bounds__(256) k_det_reduce(const uint32_t* __restrict__
     }
 }
 
-__global__ void k_det_loss(const double* __restrict__ parts, int64_t n, int accumulate, double* __restrict__ out)
+// The objective partials, added in an order that their number alone fixes:
+// thread i takes slots i, i + 1024, ... in turn, then a tree over the threads.
+// (One thread adding them all took 326 us for 6144 partials: a chain of
+// dependent loads and adds.)
+__global__ void __launch_bounds__(1024) k_det_loss(const double* __restrict__ parts, int64_t n, int accumulate,
+                                                   double* __restrict__ out)
 {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    __shared__ double sum[1024];
     double s = 0.0;
-    for (int64_t i = 0; i < n; ++i) s += parts[i];
-    *out = accumulate ? *out + s : s;
+    for (int64_t i = threadIdx.x; i < n; i += 1024) s += parts[i];
+    sum[threadIdx.x] = s;
+    for (int h = 512; h >= 1; h >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < h) sum[threadIdx.x] += sum[threadIdx.x + h];
+    }
+    if (threadIdx.x == 0) *out = accumulate ? *out + sum[0] : sum[0];
 }
 
 constexpr int64_t kDetLossSlots = 1 << 16;
@@ -309,7 +319,7 @@ gcp_status launch_det(gcp_tensor_s* t, const gcp_sample_params* sp, const void* 
     GCP_HIP(hipGetLastError());
     // 6. the objective, partials in slot order
     if (loss_out) {
-        hipLaunchKernelGGL(k_det_loss, dim3(1), dim3(64), 0, stream, (const double*)(ws + L.parts), parts,
+        hipLaunchKernelGGL(k_det_loss, dim3(1), dim3(1024), 0, stream, (const double*)(ws + L.parts), parts,
                            accumulate ? 1 : 0, loss_out);
         GCP_HIP(hipGetLastError());
     }
