@@ -64,7 +64,6 @@ struct FedArgs {
     const int* cov_client;
     const int* cov_lrow;           // the row's index in the client's model
     T* const* Mptrs;               // per client model
-    int staging_bytes;             // LDS before the private gradient copies
 };
 
 __device__ __forceinline__ bool barrier_failed(const uint32_t* status)
@@ -125,10 +124,7 @@ __global__ void __launch_bounds__(1024) k_fed_clients(const FedArgs<T> F)
     const int64_t nparams = C.nparams;
     const int nwaves = blockDim.x >> 6;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint64_t* skey = reinterpret_cast<uint64_t*>(smem) + wave * 64;
-    T* sx = reinterpret_cast<T*>(smem + (size_t)nwaves * 64 * 8) + wave * 64;
-    T* sw = reinterpret_cast<T*>(smem + (size_t)nwaves * 64 * (8 + sizeof(T))) + wave * 64;
-    T* priv = reinterpret_cast<T*>(smem + F.staging_bytes);
+    T* priv = reinterpret_cast<T*>(smem);
     const int64_t round = *F.round;
     const int64_t tid = (int64_t)w * blockDim.x + threadIdx.x;
     const int64_t nthreads = (int64_t)F.W * blockDim.x;
@@ -150,8 +146,8 @@ __global__ void __launch_bounds__(1024) k_fed_clients(const FedArgs<T> F)
             __syncthreads();
         }
         for (int64_t chunk = (int64_t)w * nwaves + wave; chunk < P.nchunks; chunk += (int64_t)F.W * nwaves)
-            lg_chunk<T, D, LANES, VEC, 0>(P, chunk, lane, skey, sx, sw, priv, nullptr, nullptr, 0, false, T(1),
-                                          lacc, step);
+            lg_chunk<T, D, LANES, VEC, true>(P, chunk * 64, LANES, lane, priv, nullptr, nullptr, 0, false, T(1), lacc,
+                                             step);
         if (P.lds_mask) {
             // flush this workgroup's share of the small modes' gradient once
             __syncthreads();
@@ -187,7 +183,7 @@ __global__ void __launch_bounds__(1024) k_fed_clients(const FedArgs<T> F)
 // samples, forms model values and derivatives, accumulates the small modes in
 // its LDS, and sorts the block by row block into the client's segment list
 // of the same index; the small modes are flushed into G_c once at the end.
-template <typename T, int D, int LANES, int VEC>
+template <typename T, int D, int LANES, int VEC, bool SCATTER>
 __global__ void __launch_bounds__(1024) k_fed_sample(const FedArgs<T> F, int j)
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
@@ -195,10 +191,7 @@ __global__ void __launch_bounds__(1024) k_fed_sample(const FedArgs<T> F, int j)
     const LGParams<T> P = F.clients[blockIdx.y].P;
     const int nwaves = blockDim.x >> 6;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint64_t* skey = reinterpret_cast<uint64_t*>(smem) + wave * 64;
-    T* sx = reinterpret_cast<T*>(smem + (size_t)nwaves * 64 * 8) + wave * 64;
-    T* sw = reinterpret_cast<T*>(smem + (size_t)nwaves * 64 * (8 + sizeof(T))) + wave * 64;
-    T* priv = reinterpret_cast<T*>(smem + F.staging_bytes);
+    T* priv = reinterpret_cast<T*>(smem);
     uint64_t* bkey = reinterpret_cast<uint64_t*>(smem + P.bucket_lds);
     T* by = reinterpret_cast<T*>(smem + P.bucket_lds + (size_t)P.spb * 8);
     int* bcnt = reinterpret_cast<int*>(smem + P.bucket_lds + (size_t)P.spb * (8 + sizeof(T)));
@@ -212,9 +205,9 @@ __global__ void __launch_bounds__(1024) k_fed_sample(const FedArgs<T> F, int j)
     }
     for (int64_t jb = blockIdx.x; jb < P.nblocks; jb += gridDim.x) {
         const int64_t s0 = jb * P.spb;
-        const int64_t c_end = std::min<int64_t>(P.nchunks, (s0 + P.spb) / 64);
-        for (int64_t chunk = s0 / 64 + wave; chunk < c_end; chunk += nwaves)
-            lg_chunk<T, D, LANES, VEC, 0>(P, chunk, lane, skey, sx, sw, priv, bkey, by, s0, true, T(1), lacc, step);
+        const int64_t s_end = std::min<int64_t>(P.n, s0 + P.spb);
+        for (int64_t s = s0 + (int64_t)wave * 64; s < s_end; s += (int64_t)nwaves * 64)
+            lg_chunk<T, D, LANES, VEC, SCATTER>(P, s, LANES, lane, priv, bkey, by, s0, true, T(1), lacc, step);
         bucket_write_out<T, D>(P, jb, (int)std::min<int64_t>(P.spb, P.n - s0), bkey, by, bcnt, boff);
     }
     if (P.lds_mask) {
@@ -351,10 +344,10 @@ static FedKernel<T> pick_fed(int lanes, int vec)
 }
 
 template <typename T, int D>
-static FedStepKernel<T> pick_fed_sample(int lanes, int vec)
+static FedStepKernel<T> pick_fed_sample(bool scatter, int lanes, int vec)
 {
 #define GCP_CASE(LN, VC) \
-    if (lanes == LN && vec == VC) return k_fed_sample<T, D, LN, VC>;
+    if (lanes == LN && vec == VC) return scatter ? k_fed_sample<T, D, LN, VC, true> : k_fed_sample<T, D, LN, VC, false>;
     if constexpr (sizeof(T) == 4) {
         GCP_FED_SHAPES_F32(GCP_CASE)
     } else {
@@ -478,7 +471,6 @@ static gcp_status fed_build(gcp_fed_s* f)
     }
     f->lds_mask = lds_mask;
     f->lds_bytes = (size_t)lds_max_elems * sizeof(T);
-    const size_t staging = (size_t)(f->block / 64) * 64 * (8 + 2 * sizeof(T));
 
     // row-bucketed modes of the batched kernel: a row block of 2^br_shift rows
     // fills kFedBucketRowBytes of LDS; each client sorts its samples in blocks
@@ -514,7 +506,7 @@ static gcp_status fed_build(gcp_fed_s* f)
         f->bucket_mask = bucket_mask;
         f->spb = spb;
         f->nb_max = nb_max;
-        f->sample_lds = ((staging + f->lds_bytes + 15) & ~(size_t)15) + (size_t)spb * (8 + sizeof(T)) + (size_t)nb_max * 8;
+        f->sample_lds = ((f->lds_bytes + 15) & ~(size_t)15) + (size_t)spb * (8 + sizeof(T)) + (size_t)nb_max * 8;
         f->owner_lds = ((((size_t)1 << br_shift) * R * sizeof(T) + 15) & ~(size_t)15) + (size_t)nblocks_c * 8;
     }
     for (int c = 0; c < K; ++c) {
@@ -538,7 +530,6 @@ static gcp_status fed_build(gcp_fed_s* f)
         h.P.G = (T*)cl.G;
         h.P.R = R;
         h.P.loss = D.loss;
-        for (int k = 0; k < kMaxModes; ++k) h.P.rowoff[k] = k < d ? t->rowoff[k] : t->rowoff[d];
         for (int k = 0; k <= kMaxModes; ++k) h.P.bucket_base[k] = 0;
         h.P.lds_mask = lds_mask;
         int64_t off = 0;
@@ -549,6 +540,7 @@ static gcp_status fed_build(gcp_fed_s* f)
             }
         }
         h.P.lds_elems = off;
+        set_row_offsets(h.P, t);
         if (bucket_mask) {
             h.P.bucket_mask = bucket_mask;
             h.P.n_bucket_modes = nbm;
@@ -557,7 +549,7 @@ static gcp_status fed_build(gcp_fed_s* f)
             h.P.spb = spb;
             h.P.nblocks = nblocks_c;
             h.P.entry_cap = (int64_t)spb * nbm;
-            h.P.bucket_lds = (int)((staging + f->lds_bytes + 15) & ~(size_t)15);
+            h.P.bucket_lds = (int)((f->lds_bytes + 15) & ~(size_t)15);
             int nb = 0;
             for (int k = 0; k < d; ++k) {
                 h.P.bucket_base[k] = nb;
@@ -638,10 +630,11 @@ static gcp_status fed_build(gcp_fed_s* f)
     memcpy(f->args, &a, sizeof(a));
 
     bool order3 = d == 3;
-    for (const gcp_fed_client& cl : f->clients) order3 = order3 && kernel_order(cl.tensor) == 3;
+    for (const gcp_fed_client& cl : f->clients) order3 = order3 && kernel_order(cl.tensor, R, f->bucketed) == 3;
     if (D.batched && f->bucketed) {
-        reinterpret_cast<FedArgs<T>*>(f->args)->staging_bytes = (int)staging;
-        FedStepKernel<T> sk = order3 ? pick_fed_sample<T, 3>(f->lanes, f->vec) : pick_fed_sample<T, 0>(f->lanes, f->vec);
+        const bool scatter = bucket_mask != (1u << d) - 1;   // some mode is LDS-private or atomic
+        FedStepKernel<T> sk = order3 ? pick_fed_sample<T, 3>(scatter, f->lanes, f->vec)
+                                     : pick_fed_sample<T, 0>(scatter, f->lanes, f->vec);
         FedKernel<T> ok = order3 ? pick_fed_owner<T, 3>(f->lanes, f->vec) : pick_fed_owner<T, 0>(f->lanes, f->vec);
         if (!sk || !ok)
             return set_error(GCP_ERR_UNSUPPORTED, "batched lane shape lanes = %d, vec = %d not built", f->lanes, f->vec);
@@ -669,8 +662,7 @@ static gcp_status fed_build(gcp_fed_s* f)
         if (!kern) return set_error(GCP_ERR_UNSUPPORTED, "batched lane shape lanes = %d, vec = %d not built", f->lanes,
                                     f->vec);
         f->client_kernel = reinterpret_cast<const void*>(kern);
-        f->client_lds = staging + f->lds_bytes;
-        reinterpret_cast<FedArgs<T>*>(f->args)->staging_bytes = (int)staging;
+        f->client_lds = f->lds_bytes;
         st = prepare_lds(f->client_kernel, f->client_lds, f->device);
         if (st != GCP_OK) return st;
         int per_cu = 0;

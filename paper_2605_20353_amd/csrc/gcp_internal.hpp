@@ -83,11 +83,16 @@ struct gcp_tensor_s {
 };
 
 namespace gcp {
-// Order the kernels are specialised for: 3 and 4 have their own builds, every
-// other order -- and every mixed-radix key layout -- runs the general one (0).
-inline int kernel_order(const gcp_tensor_s* t)
+// Order the kernels are specialised for: 3, 4 and 5 have their own builds, every
+// other order runs the general one (0).  The specialised ones address the
+// model with 32-bit byte offsets, so models of 4 GiB and more run the general
+// one too; so do bucketed calls on tensors with mixed-radix keys, since the
+// sort and the owner pass of the specialised ones unpack keys by shifts.
+inline int kernel_order(const gcp_tensor_s* t, int R, bool bucketed)
 {
-    return (t->layout.radix || (t->d != 3 && t->d != 4)) ? 0 : t->d;
+    if (t->d < 3 || t->d > 5 || (bucketed && t->layout.radix)) return 0;
+    const uint64_t row = (uint64_t)R * (t->dt == GCP_F32 ? 4 : 8);
+    return (uint64_t)t->rowoff[t->d] <= 0xffffffffull / row ? t->d : 0;
 }
 }  // namespace gcp
 
@@ -115,8 +120,14 @@ struct U64x4 {
 __host__ __device__ __forceinline__ void mul_hilo64(uint64_t a, uint64_t b, uint64_t& hi, uint64_t& lo)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    lo = a * b;
-    hi = __umul64hi(a, b);
+    // four 32 x 32 -> 64 multiply-adds give both halves (a low and a high
+    // product formed apart take seven)
+    const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+    const uint64_t t0 = (uint64_t)a0 * b0;
+    const uint64_t t1 = (uint64_t)a1 * b0 + (t0 >> 32);
+    const uint64_t t2 = (uint64_t)a0 * b1 + (uint32_t)t1;
+    hi = (uint64_t)a1 * b1 + (t1 >> 32) + (t2 >> 32);
+    lo = (t2 << 32) | (uint32_t)t0;
 #else
     unsigned __int128 p = (unsigned __int128)a * b;
     lo = (uint64_t)p;
@@ -129,6 +140,11 @@ __host__ __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1
 {
     constexpr uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
     constexpr uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
+#if defined(__HIP_DEVICE_COMPILE__)
+    // the key schedule stays with the rounds: hoisted out of a sample loop, its
+    // twenty 64-bit words would not fit the scalar registers and spill
+    asm volatile("" : "+s"(k0), "+s"(k1));
+#endif
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         uint64_t hi0, lo0, hi1, lo1;
@@ -154,6 +170,13 @@ __host__ __device__ __forceinline__ uint64_t range_map(uint64_t u, uint64_t n)
 #else
     return (uint64_t)(((unsigned __int128)u * n) >> 64);
 #endif
+}
+
+// The same for n < 2^32 in two multiplies: floor((u1 n + floor(u0 n / 2^32)) / 2^32).
+__host__ __device__ __forceinline__ uint32_t range_map32(uint64_t u, uint32_t n)
+{
+    const uint64_t low = (uint64_t)(uint32_t)u * n;
+    return (uint32_t)(((u >> 32) * n + (low >> 32)) >> 32);
 }
 
 enum : uint64_t { kStreamNonzero = 0, kStreamZero = 1, kStreamUniform = 2 };
@@ -218,26 +241,6 @@ __host__ __device__ __forceinline__ void unpack_all(const KeyLayout& L, int dd, 
         }
         c[0] = (uint32_t)key;
     }
-}
-
-// Candidate cell of sample s / attempt a drawn straight into a cell key.
-template <int D>
-__device__ __forceinline__ uint64_t draw_cell_key(const KeyLayout& L, int d, uint64_t seed, uint64_t client,
-                                                  uint64_t s, uint64_t step, uint64_t stream, uint64_t attempt)
-{
-    const int dd = D > 0 ? D : d;
-    uint64_t key = 0;
-    U64x4 o = philox4x64_10(s, step, stream | (attempt << 8), 0, seed, client);
-#pragma unroll
-    for (int k = 0; k < (D > 0 ? (D < 4 ? D : 4) : 4); ++k)
-        if (k < dd) key += pack_coord<D == 0>(L, range_map(o.v[k], (uint64_t)L.dims[k]), k);
-    if (dd > 4) {
-        U64x4 o2 = philox4x64_10(s, step, stream | (attempt << 8), 1, seed, client);
-#pragma unroll
-        for (int k = 4; k < kMaxModes; ++k)
-            if (k < dd) key += pack_coord<D == 0>(L, range_map(o2.v[k - 4], (uint64_t)L.dims[k]), k);
-    }
-    return key;
 }
 
 // ------------------------------------------------------ membership table --

@@ -12,13 +12,19 @@ template <typename T>
 struct LGParams {
     SampleCtx<T> sc;
     int64_t n;            // samples p + q
-    int64_t nchunks;      // ceil(n / 64)
-    const int64_t* m_coords;  // materialised list (SRC = 1, 3)
+    int64_t nchunks;      // ceil(n / chunk_samples)
+    const int64_t* m_coords;  // materialised list (src = 1, 3)
     const T* m_x;
     const T* m_w;
     const T* A;
     T* G;
     int R;
+    int src;              // where the samples come from (lg_chunk)
+    int passes;           // samples per lane group and chunk: a chunk has 64 / lanes * passes samples
+    int chunk_samples;
+    uint32_t stride_b;              // bytes of a model row
+    uint32_t rowb[kMaxModes];       // order-specific kernels: byte offset of each mode's first row (models below 4 GiB)
+    uint32_t ldsb[kMaxModes];       // the same, from a row's byte offset in A to its LDS-private copy (modulo 2^32)
     int loss;
     int loss_only;
     int semi;             // semi-stratified: samples s < p get f'(x,m) - f'(0,m)
@@ -28,7 +34,6 @@ struct LGParams {
     uint32_t lds_mask;    // modes accumulated in LDS
     int64_t lds_off[kMaxModes];
     int64_t lds_elems;
-    int staging_bytes;
     // bucketed scatter
     uint32_t bucket_mask;      // modes scattered through row-block buckets
     int n_bucket_modes;
@@ -47,7 +52,7 @@ struct LGParams {
     int64_t bwg_base[kMaxModes + 1];
     int bsplits[kMaxModes];
     int bsegs[kMaxModes];
-    // non-fused sampling step (SRC = 2): each sample's y, the sampled
+    // non-fused sampling step (src = 2): each sample's y, the sampled
     // tensor's values, and its coordinates [n x d], written instead of
     // scattering (last, so that the fields above keep their kernel-argument
     // offsets)
@@ -58,11 +63,18 @@ struct LGParams {
     double* loss_parts;
 };
 
-__device__ __forceinline__ void wave_sync()
+// Row offsets of the launch from the tensor's dims (P.lds_mask and P.lds_off
+// set before): row indexes for the any-order kernels, byte offsets modulo 2^32
+// for the order-specific ones.
+template <typename T>
+inline void set_row_offsets(LGParams<T>& P, const gcp_tensor_s* t)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    P.stride_b = (uint32_t)P.R * (uint32_t)sizeof(T);
+    for (int k = 0; k < kMaxModes; ++k) {
+        P.rowoff[k] = k < t->d ? t->rowoff[k] : t->rowoff[t->d];
+        P.rowb[k] = (uint32_t)P.rowoff[k] * P.stride_b;
+        P.ldsb[k] = (uint32_t)P.lds_off[k] * (uint32_t)sizeof(T) - P.rowb[k];
+    }
 }
 
 template <typename T, int V>
@@ -200,6 +212,82 @@ __device__ __forceinline__ double xor_shfl(double v, int mask)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Value of lane (at / 4) of the wavefront (at: byte address of a lane, as
+// bpermute takes it).
+__device__ __forceinline__ float lane_from(float v, int at)
+{
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(v)));
+}
+__device__ __forceinline__ double lane_from(double v, int at)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_ds_bpermute(at, (int)(b & 0xffffffffll));
+    const int hi = __builtin_amdgcn_ds_bpermute(at, (int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// DPP lane exchange of a whole wavefront (every lane has a source lane).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Sum over the aligned group of LANES lanes, in every lane of it: a butterfly
+// from the farthest exchange to the nearest.  From 16 lanes on, the exchanges
+// 8 and 4 apart are row rotations (the row repeats with the period of the
+// step before); in a group of 8, lane ^ 4 is a quad reversal then a half-row
+// mirror.  All are DPP operands of VALU instructions: only the 32- and
+// 64-lane groups take trips through the LDS crossbar.
+template <int LANES, typename T>
+__device__ __forceinline__ T group_sum(T v)
+{
+    if constexpr (LANES >= 64) v += xor_shfl(v, 32);
+    if constexpr (LANES >= 32) v += xor_shfl(v, 16);
+    if constexpr (LANES >= 16) {
+        v += dpp<0x128>(v);                            // row_ror:8
+        v += dpp<0x124>(v);                            // row_ror:4
+    } else if constexpr (LANES == 8) {
+        v += dpp<0x141>(dpp<0x1B>(v));                 // quad_perm [3,2,1,0], row_half_mirror
+    }
+    if constexpr (LANES >= 4) v += dpp<0x4E>(v);       // quad_perm [2,3,0,1]
+    if constexpr (LANES >= 2) v += dpp<0xB1>(v);       // quad_perm [1,0,3,2]
+    return v;
+}
+
+// The value of lane u (mod U) of each aligned run of U lanes, U = 1, 2 or 4.
+template <int U, typename T>
+__device__ __forceinline__ T quad_pick(T v, int u)
+{
+    if constexpr (U == 1) return v;
+    else if constexpr (U == 2) return u == 0 ? dpp<0xA0>(v) : dpp<0xF5>(v);
+    else return u == 0 ? dpp<0x00>(v) : u == 1 ? dpp<0x55>(v) : u == 2 ? dpp<0xAA>(v) : dpp<0xFF>(v);
+}
+
+// Derivative value of one sample (x, w, model value m); l receives its part
+// of the objective when one is asked for.  nonzero: the sample is one of the
+// first p.
+template <typename T>
+__device__ __forceinline__ T sample_y(const LGParams<T>& P, T x, T w, T m, bool nonzero, T& l)
+{
+    const bool semi_nz = P.semi && nonzero;
+    T y = w * loss_df<T>(P.loss, x, m);
+    if (semi_nz) y -= w * loss_df<T>(P.loss, T(0), m);
+    if (P.loss_out) {
+        l = w * loss_f<T>(P.loss, x, m);
+        if (semi_nz) l -= w * loss_f<T>(P.loss, T(0), m);
+    }
+    return y;
+}
+
 // Exclusive prefix sum of cnt[0, n) into off[0, n) by one wavefront.
 __device__ inline void wave_exclusive_scan(const int* cnt, int* off, int n, int lane)
 {
@@ -223,19 +311,14 @@ __device__ inline void wave_exclusive_scan(const int* cnt, int* off, int n, int 
     }
 }
 
-// Samples per lane group whose factor-row gathers are issued together.  It
-// must divide LANES: a pass covers samples it*S+g .. (it+U-1)*S+g of the
-// wave's 64 staged samples, so a U that does not divide LANES would read past
-// the staging slice on the last pass.
+// Samples per lane group whose factor-row gathers are issued together; divides
+// LANES.  The scattering form also holds the rows until its products are out.
 #ifndef GCP_UNROLL_WIDE
 #define GCP_UNROLL_WIDE 2
 #endif
-template <typename T, int D, int LANES, int VEC>
-constexpr int samples_in_flight()
+constexpr int samples_in_flight(int order, int elem_bytes, int lanes, int vec)
 {
-    constexpr int U = (D == 0 || LANES < 4) ? 1 : sizeof(T) == 8 ? 2 : VEC == 4 ? GCP_UNROLL_WIDE : 4;
-    static_assert(U >= 1 && LANES % U == 0, "samples in flight must divide the lanes per sample");
-    return U;
+    return (order == 0 || lanes < 4) ? 1 : elem_bytes == 8 ? 2 : vec == 4 ? GCP_UNROLL_WIDE : 4;
 }
 
 // Entries in flight per lane group in the owner pass of the bucketed scatter
@@ -251,204 +334,212 @@ constexpr int owner_in_flight()
     return U;
 }
 
-// One chunk of 64 samples: phase 1 (one lane per sample: draw or read the
-// sample, stage it in the wave's LDS slice) and phase 2 (LANES lanes per
-// sample: gather rows, model value, loss derivative, scatter).  Shared by the
-// sampled-gradient kernel and the batched GCP-FedAdam kernel.
-//   SRC = 0  draw the samples (the fused sampled gradient);
-//   SRC = 1  read a materialised sample list (coordinates, x, w);
-//   SRC = 2  draw the samples and write the sampled tensor (coordinates and
-//            y = w f'(x, m)) instead of scattering: the sampling step of the
-//            non-fused gradient;
-//   SRC = 3  read a sampled tensor whose values are already y (w = 1 unless a
-//            weight list is given): the MTTKRP step of the non-fused gradient.
-template <typename T, int D, int LANES, int VEC, int SRC>
-__device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t chunk, int lane, uint64_t* skey, T* sx,
-                                         T* sw, T* priv, uint64_t* bkey, T* by, int64_t block_s0, bool tiled,
-                                         T scale, double& lacc, uint64_t step)
+// One chunk of up to 64 samples by one wavefront, without LDS staging.
+//
+// Phase 1, one lane per sample: draw or read the sample and turn its
+// coordinates into the d factor rows' offsets.  Lane group g (LANES lanes)
+// owns the chunk's samples g * passes + cl, cl < passes; passes is
+// LANES for a full chunk of 64 and less when a call has too few samples to
+// fill the GPU with full chunks.
+// Phase 2, LANES lanes per sample: in pass `it` each group works on the sample
+// its own lane `it` drew -- the row offsets come from that lane by bpermute,
+// so the key is unpacked and the address products are formed once per sample
+// instead of once per lane -- gathers the rows (every load unconditional:
+// inactive samples read row 0, lanes past column R read column 0; a load under
+// a branch makes the compiler wait for every load before it), and reduces the
+// model value over the group by DPP adds.
+//   SCATTER = false: nothing is scattered in the loop (objective only, the
+//     sampled tensor is written, or every mode is bucketed): lane `it` keeps
+//     its sample's model value and, after the loop, each lane evaluates the
+//     loss of its own sample -- once per sample, not once per lane.
+//   SCATTER = true: the U samples of a pass are evaluated by lanes cl % U and
+//     y is handed back by a quad broadcast; then the leave-one-out products go
+//     to the LDS-private copies or to G by atomics.
+// Bound by the draw's random reads (2^21 samples of 10000x8000x6000, 5e7
+// nonzeros: 66 us to draw alone, 81 us with the gathers and the objective
+// where the form that unpacked keys and evaluated losses in every lane and
+// staged samples through LDS took 98 us) and, with sorting, by its stores.
+// P.src: 0 draw the samples (the fused sampled gradient); 1 read a
+// materialised list (coordinates, x, w); 2 draw and write the sampled tensor
+// (coordinates and y = w f'(x, m)): the sampling step of the non-fused
+// gradient; 3 read a sampled tensor whose values are already y (w = 1 unless a
+// weight list is given): the MTTKRP step of the non-fused gradient.
+template <typename T, int D, int LANES, int VEC, bool SCATTER>
+__device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int passes, int lane, T* priv,
+                                         uint64_t* bkey, T* by, int64_t block_s0, bool tiled, T scale, double& lacc,
+                                         uint64_t step)
 {
-    constexpr int S = 64 / LANES;                  // samples per pass
-    constexpr int U = samples_in_flight<T, D, LANES, VEC>();
+    constexpr int U = samples_in_flight(D, (int)sizeof(T), LANES, VEC);
+    static_assert(LANES % U == 0, "samples in flight must divide the lanes per sample");
     constexpr int DM = D > 0 ? D : kMaxModes;
     const int dd = D > 0 ? D : P.sc.d;
     const int R = P.R;
     const int g = lane / LANES, cl = lane % LANES;
     const int col0 = cl * VEC;
     const bool col_ok = col0 < R;          // VEC divides R
-    const int64_t s0 = chunk * 64;
-    {   // phase 1: one lane per sample
-        const int64_t s = s0 + lane;
-        uint64_t key = 0;
-        T x = T(0), w = T(0);
-        if (s < P.n) {
-            if constexpr (SRC == 0 || SRC == 2) {
-                draw_sample<T, D>(P.sc, step, s, key, x, w);
+    const int colL = col_ok ? col0 : 0;
+    const uint32_t colb = (uint32_t)colL * (uint32_t)sizeof(T);
+
+    // phase 1
+    const int64_t s = s0 + g * passes + cl;
+    const bool mine = cl < passes && s < P.n;
+    uint64_t key = 0;
+    uint32_t off[DM];                      // D > 0: byte offset of the row in A; else its row index
+    T x = T(0), w = T(0);
+    {
+        uint32_t ci[DM];
+#pragma unroll
+        for (int k = 0; k < DM; ++k) ci[k] = 0;
+        if (mine) {
+            if (P.src == 0 || P.src == 2) {
+                draw_sample<T, D>(P.sc, step, s, key, ci, x, w);
             } else {
                 bool ok = true;
 #pragma unroll
                 for (int k = 0; k < DM; ++k) {
                     if (k < dd) {
-                        int64_t c = P.m_coords[s * dd + k];
+                        const int64_t c = P.m_coords[s * dd + k];
                         if (c < 0 || c >= P.sc.L.dims[k]) ok = false;
-                        else key += pack_coord<D == 0>(P.sc.L, (uint64_t)c, k);
+                        else ci[k] = (uint32_t)c;
                     }
                 }
                 x = P.m_x[s];
                 w = P.m_w ? P.m_w[s] : T(1);
                 if (!ok) {
                     atomicOr(P.sc.status, kStatusData);
-                    key = 0;
+#pragma unroll
+                    for (int k = 0; k < DM; ++k) ci[k] = 0;
                     w = T(0);
                 }
+#pragma unroll
+                for (int k = 0; k < DM; ++k)
+                    if (k < dd) key += pack_coord(P.sc.L, (uint64_t)ci[k], k);
             }
+            if (P.src == 2) {
+#pragma unroll
+                for (int k = 0; k < DM; ++k)
+                    if (k < dd) P.c_out[s * dd + k] = (int64_t)ci[k];
+            }
+            if (tiled) bkey[s - block_s0] = key;
         }
-        skey[lane] = key;
-        sx[lane] = x;
-        sw[lane] = w;
+#pragma unroll
+        for (int k = 0; k < DM; ++k) {
+            if constexpr (D > 0) off[k] = P.rowb[k] + ci[k] * P.stride_b;
+            else off[k] = (uint32_t)P.rowoff[k] + ci[k];
+        }
     }
-    wave_sync();
-    // phase 2: LANES lanes per sample, U samples per lane group in flight
-    for (int it = 0; it < LANES; it += U) {
-        uint64_t key[U];
-        T a[U][DM][VEC];
+    const bool given = P.src == 3;
+    const int from0 = (lane & ~(LANES - 1)) << 2;   // bpermute address of the group's first lane
+    T mown = T(0);
+
+    if (SCATTER || !given) {
+        for (int it = 0; it < passes; it += U) {
+            uint32_t o[U][DM];
+            T a[U][DM][VEC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int slot = (it + u) * S + g;
-            const bool valid = s0 + slot < P.n;
-            key[u] = skey[slot];
-            uint32_t ci[DM];
-            unpack_all<D == 0>(P.sc.L, dd, key[u], ci);
+            for (int u = 0; u < U; ++u) {
 #pragma unroll
-            for (int k = 0; k < DM; ++k) {
-                if (k < dd) {
-                    const uint64_t row = (uint64_t)P.rowoff[k] + ci[k];
-                    if (col_ok && valid) {
-                        load_cols<T, VEC>(P.A + row_elem(row, R) + col0, a[u][k]);
+                for (int k = 0; k < DM; ++k)
+                    if (k < dd) o[u][k] = (uint32_t)__builtin_amdgcn_ds_bpermute(from0 + ((it + u) << 2), (int)off[k]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int k = 0; k < DM; ++k) {
+                    if (k < dd) {
+                        if constexpr (D > 0)
+                            load_cols<T, VEC>(reinterpret_cast<const T*>(reinterpret_cast<const char*>(P.A) +
+                                                                         (o[u][k] + colb)),
+                                              a[u][k]);
+                        else
+                            load_cols<T, VEC>(P.A + row_elem(o[u][k], R) + colL, a[u][k]);
+                    }
+                }
+            }
+            T m[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                T part = T(0);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    T prod = a[u][0][v];
+#pragma unroll
+                    for (int k = 1; k < DM; ++k)
+                        if (k < dd) prod *= a[u][k][v];
+                    if constexpr (D == 5) {
+                        // rounded after the product, as in the any-order kernel
+#pragma clang fp contract(off)
+                        part = part + prod;
                     } else {
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) a[u][k][v] = T(0);
+                        part += prod;
                     }
                 }
+                m[u] = group_sum<LANES>(col_ok ? part : T(0));
             }
-        }
-        T m[U];
+            if constexpr (!SCATTER) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            T part = T(0);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                T prod = a[u][0][v];
-#pragma unroll
-                for (int k = 1; k < DM; ++k)
-                    if (k < dd) prod *= a[u][k][v];
-                part += prod;
-            }
-            m[u] = part;
-        }
-#pragma unroll
-        for (int off = LANES / 2; off >= 1; off >>= 1) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) m[u] += xor_shfl(m[u], off);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int slot = (it + u) * S + g;
-            const int64_t s = s0 + slot;
-            if (s >= P.n) continue;
-            const T x = sx[slot], w = sw[slot];
-            T y;
-            if constexpr (SRC == 3) {
-                y = w * x;
+                for (int u = 0; u < U; ++u) mown = cl == it + u ? m[u] : mown;
             } else {
-                const bool semi_nz = P.semi && s < P.sc.p;
-                y = w * loss_df<T>(P.loss, x, m[u]);
-                if (semi_nz) y -= w * loss_df<T>(P.loss, T(0), m[u]);
-                if (P.loss_out && cl == 0) {
-                    T l = w * loss_f<T>(P.loss, x, m[u]);
-                    if (semi_nz) l -= w * loss_f<T>(P.loss, T(0), m[u]);
-                    lacc += (double)l;
-                }
-            }
-            if constexpr (SRC == 2) {
-                // the sampled tensor Y~ goes to memory; nothing is scattered
-                if (cl == 0) {
-                    uint32_t ci[DM];
-                    unpack_all<D == 0>(P.sc.L, dd, key[u], ci);
+                // lane cl evaluates sample it + cl % U of its group
+                const int ul = cl & (U - 1);
+                const int at = it + ul;
+                const int64_t sl = s0 + g * passes + at;
+                const T xl = lane_from(x, from0 + (at << 2));
+                const T wl = lane_from(w, from0 + (at << 2));
+                T ml = m[0];
 #pragma unroll
-                    for (int k = 0; k < DM; ++k)
-                        if (k < dd) P.c_out[s * dd + k] = (int64_t)ci[k];
-                    P.y_out[s] = y;
-                }
-                continue;
-            }
-            if (P.loss_only) continue;
-            y *= scale;
-            if (tiled && cl == 0) {
-                bkey[s - block_s0] = key[u];
-                by[s - block_s0] = y;
-            }
-            // all modes bucketed: the owner pass forms the products
-            if (!col_ok || P.bucket_mask == (1u << dd) - 1) continue;
-            // coordinates again from the key (a few shifts when bit-packed),
-            // rather than holding them live across the gathers
-            uint32_t ci[DM];
-            unpack_all<D == 0>(P.sc.L, dd, key[u], ci);
-            if constexpr (sizeof(T) == 4 && VEC >= 2) {
-                // leave-one-out products y prod_{n != k} A_n[i_n, :] by prefix
-                // and suffix running products, then per mode not bucketed:
-                // added to the LDS-private copy (column pairs) or to G by
-                // global atomics
-                T cv[DM][VEC];
+                for (int u = 1; u < U; ++u) ml = ul == u ? m[u] : ml;
+                const bool vl = at < passes && sl < P.n;
+                T l = T(0);
+                T y = given ? wl * xl : sample_y<T>(P, xl, wl, ml, sl < P.sc.p, l);
+                if (vl && cl < U) lacc += (double)l;
+                y *= scale;
+                if (tiled && vl && cl < U) by[sl - block_s0] = y;
+                T yu[U];
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    T pre[DM];
-                    pre[0] = y;
+                for (int u = 0; u < U; ++u) yu[u] = quad_pick<U>(y, u);
 #pragma unroll
-                    for (int k = 1; k < DM; ++k)
-                        if (k < dd) pre[k] = pre[k - 1] * a[u][k - 1][v];
-                    T suf = T(1);
+                for (int u = 0; u < U; ++u) {
+                    if (it + u >= passes || s0 + g * passes + it + u >= P.n || !col_ok) continue;
+                    // leave-one-out products y prod_{n != k} A_n[i_n, :] by
+                    // prefix and suffix running products
+                    T cv[DM][VEC];
 #pragma unroll
-                    for (int k = DM - 1; k >= 0; --k) {
-                        if (k < dd) {
-                            cv[k][v] = pre[k] * suf;
-                            suf *= a[u][k][v];
+                    for (int v = 0; v < VEC; ++v) {
+                        T pre[DM];
+                        pre[0] = yu[u];
+#pragma unroll
+                        for (int k = 1; k < DM; ++k)
+                            if (k < dd) pre[k] = pre[k - 1] * a[u][k - 1][v];
+                        T suf = T(1);
+#pragma unroll
+                        for (int k = DM - 1; k >= 0; --k) {
+                            if (k < dd) {
+                                cv[k][v] = pre[k] * suf;
+                                suf *= a[u][k][v];
+                            }
                         }
                     }
-                }
-#pragma unroll
-                for (int k = DM - 1; k >= 0; --k) {
-                    if (k < dd && !((P.bucket_mask >> k) & 1u)) {
-                        const uint32_t i = ci[k];
-                        if ((P.lds_mask >> k) & 1u) {
-                            lds_add_cols<T, VEC>(priv + P.lds_off[k] + i * (uint32_t)R + col0, cv[k]);
-                        } else {
-#pragma unroll
-                            for (int v = 0; v < VEC; ++v)
-                                global_add(P.G + row_elem((uint64_t)P.rowoff[k] + i, R) + col0 + v, cv[k][v]);
-                        }
-                    }
-                }
-            } else {
-                // no column pairs: each product goes out as soon as it is formed
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    T pre[DM];
-                    pre[0] = y;
-#pragma unroll
-                    for (int k = 1; k < DM; ++k)
-                        if (k < dd) pre[k] = pre[k - 1] * a[u][k - 1][v];
-                    T suf = T(1);
 #pragma unroll
                     for (int k = DM - 1; k >= 0; --k) {
-                        if (k < dd) {
-                            const T c = pre[k] * suf;
-                            suf *= a[u][k][v];
-                            if ((P.bucket_mask >> k) & 1u) continue;
-                            const uint32_t i = ci[k];
+                        if (k < dd && !((P.bucket_mask >> k) & 1u)) {
                             if ((P.lds_mask >> k) & 1u) {
-                                lds_add(priv + P.lds_off[k] + i * (uint32_t)R + col0 + v, c);
+                                if constexpr (D > 0)
+                                    lds_add_cols<T, VEC>(reinterpret_cast<T*>(reinterpret_cast<char*>(priv) +
+                                                                              (o[u][k] + colb + P.ldsb[k])),
+                                                         cv[k]);
+                                else
+                                    lds_add_cols<T, VEC>(priv + P.lds_off[k] +
+                                                             (o[u][k] - (uint32_t)P.rowoff[k]) * (uint32_t)R + col0,
+                                                         cv[k]);
                             } else {
-                                global_add(P.G + row_elem((uint64_t)P.rowoff[k] + i, R) + col0 + v, c);
+                                T* dst;
+                                if constexpr (D > 0)
+                                    dst = reinterpret_cast<T*>(reinterpret_cast<char*>(P.G) + (o[u][k] + colb));
+                                else
+                                    dst = P.G + row_elem(o[u][k], R) + col0;
+#pragma unroll
+                                for (int v = 0; v < VEC; ++v) global_add(dst + v, cv[k][v]);
                             }
                         }
                     }
@@ -456,7 +547,15 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t chunk, in
             }
         }
     }
-    wave_sync();
+    if constexpr (!SCATTER) {
+        if (mine) {
+            T l = T(0);
+            const T y = given ? w * x : sample_y<T>(P, x, w, mown, s < P.sc.p, l);
+            lacc += (double)l;
+            if (P.src == 2) P.y_out[s] = y;
+            if (tiled) by[s - block_s0] = y * scale;
+        }
+    }
 }
 
 // Bucketed scatter, sampling side: sorts the (key, y) of the workgroup's

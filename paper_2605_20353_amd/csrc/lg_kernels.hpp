@@ -1,8 +1,7 @@
-// Kernel templates of the sampled loss/gradient (k_loss_grad, the row-block
-// owner pass k_bucket_accum, k_zero) and the table of lane shapes they are
-// built for.  Included by the translation units that instantiate them: the
-// fused and materialised forms (loss_grad.hip) and the non-fused forms
-// (nonfused.hip).
+// Kernel templates of the sampled loss/gradient (k_loss_grad and the row-block
+// owner pass k_bucket_accum) and the table of lane shapes they are built for.
+// Instantiated per dtype and order in lg_*.hip; declared here for the host
+// side (loss_grad.hip, deterministic.hip).
 #pragma once
 
 #include <cmath>
@@ -11,24 +10,30 @@
 
 namespace gcp {
 
-template <typename T, int D, int LANES, int VEC, int SRC>
-__global__ void __launch_bounds__(1024) k_loss_grad(const LGParams<T> P)
+// Wavefronts per SIMD the register allocation aims at: the float kernels that
+// scatter nothing in their loop fit 64 VGPRs (68-76 unconstrained), and with 8
+// resident the bucketed launch's workgroups all start at once.
+template <typename T, int D, bool SCATTER>
+constexpr int lg_min_waves()
+{
+    return sizeof(T) == 4 && !SCATTER && D > 0 ? 8 : 4;
+}
+
+template <typename T, int D, int LANES, int VEC, bool SCATTER>
+__global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_grad(const LGParams<T> P)
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int nwaves = blockDim.x >> 6;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint64_t* skey = reinterpret_cast<uint64_t*>(smem) + wave * 64;
-    T* sx = reinterpret_cast<T*>(smem + (size_t)nwaves * 64 * 8) + wave * 64;
-    T* sw = reinterpret_cast<T*>(smem + (size_t)nwaves * 64 * (8 + sizeof(T))) + wave * 64;
-    T* priv = reinterpret_cast<T*>(smem + P.staging_bytes);
+    T* priv = reinterpret_cast<T*>(smem);
     // bucketed scatter staging: the workgroup's samples in order
     uint64_t* bkey = reinterpret_cast<uint64_t*>(smem + P.bucket_lds);
     T* by = reinterpret_cast<T*>(smem + P.bucket_lds + (size_t)P.spb * 8);
     int* bcnt = reinterpret_cast<int*>(smem + P.bucket_lds + (size_t)P.spb * (8 + sizeof(T)));
     int* boff = bcnt + P.nb;
 
-    if (P.lds_mask) {
+    if (SCATTER && P.lds_mask) {
         for (int64_t e = threadIdx.x; e < P.lds_elems; e += blockDim.x) priv[e] = T(0);
         __syncthreads();
     }
@@ -39,32 +44,50 @@ __global__ void __launch_bounds__(1024) k_loss_grad(const LGParams<T> P)
     const int64_t block_s0 = tiled ? (int64_t)blockIdx.x * P.spb : 0;
     double lacc = 0.0;
 
-    // tiled launches give workgroup j the chunks of samples [j*spb, (j+1)*spb)
-    int64_t chunk, chunk_end, chunk_step;
+    // tiled launches give workgroup j the samples [j*spb, (j+1)*spb)
+    const int cs = P.chunk_samples;
+    int64_t s0, s_end, s_step;
     if (tiled) {
-        chunk = block_s0 / 64 + wave;
-        chunk_end = std::min<int64_t>(P.nchunks, (block_s0 + P.spb) / 64);
-        chunk_step = nwaves;
+        s0 = block_s0 + (int64_t)wave * cs;
+        s_end = std::min<int64_t>(P.n, block_s0 + P.spb);
+        s_step = (int64_t)nwaves * cs;
     } else {
-        chunk = (int64_t)blockIdx.x * nwaves + wave;
-        chunk_end = P.nchunks;
-        chunk_step = (int64_t)gridDim.x * nwaves;
+        s0 = ((int64_t)blockIdx.x * nwaves + wave) * cs;
+        s_end = P.n;
+        s_step = (int64_t)gridDim.x * nwaves * cs;
     }
-
-    for (; chunk < chunk_end; chunk += chunk_step) {
-        lg_chunk<T, D, LANES, VEC, SRC>(P, chunk, lane, skey, sx, sw, priv, bkey, by, block_s0, tiled, scale,
-                                        lacc, P.sc.step);
+    // Each chunk reads the parameter block through a pointer that the compiler
+    // cannot see through, so that it loads a phase's fields where they are used:
+    // all of them loaded once before the loop do not fit the scalar registers,
+    // and every use then reads a spill.
+    using KernArg = const __attribute__((address_space(4))) LGParams<T>*;
+    for (; s0 < s_end; s0 += s_step) {
+        KernArg kp = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(kp));
+        const LGParams<T>& Q = *(const LGParams<T>*)kp;
+        lg_chunk<T, D, LANES, VEC, SCATTER>(Q, s0, Q.passes, lane, priv, bkey, by, block_s0, tiled, scale, lacc,
+                                            Q.sc.step);
     }
 
     if (P.loss_out) {
         for (int off = 32; off >= 1; off >>= 1) lacc += xor_shfl(lacc, off);
         if (P.loss_parts) {
             if (lane == 0) P.loss_parts[(int64_t)blockIdx.x * nwaves + wave] = lacc;
-        } else if (lane == 0 && lacc != 0.0) {
-            atomicAdd(P.loss_out, lacc);
+        } else {
+            // one add per workgroup: adds into one address are executed one
+            // after the other, about 11 ns each, and one per wavefront took
+            // 90 us at 8192 wavefronts
+            __shared__ double wave_loss[16];
+            if (lane == 0) wave_loss[wave] = lacc;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double l = 0.0;
+                for (int i = 0; i < nwaves; ++i) l += wave_loss[i];
+                if (l != 0.0) atomicAdd(P.loss_out, l);
+            }
         }
     }
-    if (P.lds_mask) {
+    if (SCATTER && P.lds_mask) {
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < DM; ++k) {
@@ -139,11 +162,11 @@ using BAKernel = void (*)(const LGParams<T>);
     X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(4, 2) X(8, 2) X(16, 2) X(32, 2) X(64, 2) X(2, 4) X(4, 4) X(8, 4) X(16, 4) X(32, 4) X(64, 4)
 #define GCP_LG_SHAPES_F64(X) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(4, 2) X(8, 2) X(16, 2) X(32, 2) X(64, 2) X(64, 4)
 
-template <typename T, int D, int SRC>
-inline LGKernel<T> pick_shape(int lanes, int vec)
+template <typename T, int D>
+inline LGKernel<T> pick_shape(bool scatter, int lanes, int vec)
 {
 #define GCP_CASE(LN, VC) \
-    if (lanes == LN && vec == VC) return k_loss_grad<T, D, LN, VC, SRC>;
+    if (lanes == LN && vec == VC) return scatter ? k_loss_grad<T, D, LN, VC, true> : k_loss_grad<T, D, LN, VC, false>;
     if constexpr (sizeof(T) == 4) {
         GCP_LG_SHAPES_F32(GCP_CASE)
     } else {
@@ -153,10 +176,44 @@ inline LGKernel<T> pick_shape(int lanes, int vec)
     return nullptr;
 }
 
-// Non-fused forms (Sec. 3.1.2), instantiated in nonfused.hip: SRC = 2 draws
-// the samples and writes the sampled tensor, SRC = 3 reads a sampled tensor
-// whose values are the derivative values.
-template <typename T>
-LGKernel<T> pick_kernel_nonfused(int d, int src, int lanes, int vec);
+template <typename T, int D>
+inline BAKernel<T> pick_bucket_shape(int lanes, int vec)
+{
+#define GCP_CASE(LN, VC) \
+    if (lanes == LN && vec == VC) return k_bucket_accum<T, D, LN, VC>;
+    if constexpr (sizeof(T) == 4) {
+        GCP_LG_SHAPES_F32(GCP_CASE)
+    } else {
+        GCP_LG_SHAPES_F64(GCP_CASE)
+    }
+#undef GCP_CASE
+    return nullptr;
+}
+
+// The kernels of order D (0: any order) at a lane shape, null when the shape
+// is not built.  scatter: the kernel that scatters in its loop (some mode is
+// LDS-private or atomic).
+template <typename T, int D>
+LGKernel<T> loss_grad_kernel(bool scatter, int lanes, int vec);
+template <typename T, int D>
+BAKernel<T> bucket_kernel(int lanes, int vec);
+
+#define GCP_LG_INSTANTIATE(T, D)                                         \
+    template <>                                                          \
+    LGKernel<T> loss_grad_kernel<T, D>(bool scatter, int lanes, int vec) \
+    {                                                                    \
+        return pick_shape<T, D>(scatter, lanes, vec);                    \
+    }                                                                    \
+    template <>                                                          \
+    BAKernel<T> bucket_kernel<T, D>(int lanes, int vec)                  \
+    {                                                                    \
+        return pick_bucket_shape<T, D>(lanes, vec);                      \
+    }
+
+#define GCP_LG_DECLARE(T, D)                                              \
+    template <>                                                           \
+    LGKernel<T> loss_grad_kernel<T, D>(bool scatter, int lanes, int vec); \
+    template <>                                                           \
+    BAKernel<T> bucket_kernel<T, D>(int lanes, int vec);
 
 }  // namespace gcp

@@ -2,14 +2,14 @@
 // "Fused Sampling-MTTKRP", here with stratified, uniform or semi-stratified
 // samples).
 //
-// Work decomposition of k_loss_grad (one 64-lane wavefront takes 64 samples
-// at a time):
+// Work decomposition of k_loss_grad (one 64-lane wavefront takes up to 64
+// samples at a time):
 //   phase 1, one lane per sample: draw the sample (Philox, nonzero record
 //     read or zero-candidate hash probes) or read it from a materialised
-//     list, and stage (cell key, x, w) in the wave's LDS slice;
+//     list, and form its d row offsets;
 //   phase 2, LANES lanes per sample with VEC consecutive columns each, 64 /
 //     LANES samples per pass and U samples per lane group in flight: gather
-//     the d factor rows, m = sum_r prod_k A_k[i_k, r] (eq. cp) by a butterfly
+//     the d factor rows, m = sum_r prod_k A_k[i_k, r] (eq. cp) by a reduction
 //     over the lane group, y = w f'(x, m), then scatter the leave-one-out
 //     products y prod_{n != k} A_n[i_n, r] into G_k[i_k, :].
 // Factor rows are read once per sample and the sampled tensor is never
@@ -33,40 +33,35 @@
 
 namespace gcp {
 
-template <typename T, int D>
-static BAKernel<T> pick_bucket_shape(int lanes, int vec)
+GCP_LG_DECLARE(float, 3)
+GCP_LG_DECLARE(float, 4)
+GCP_LG_DECLARE(float, 5)
+GCP_LG_DECLARE(float, 0)
+GCP_LG_DECLARE(double, 3)
+GCP_LG_DECLARE(double, 4)
+GCP_LG_DECLARE(double, 5)
+GCP_LG_DECLARE(double, 0)
+
+template <typename T>
+static LGKernel<T> pick_kernel(int order, bool scatter, int lanes, int vec)
 {
-#define GCP_CASE(LN, VC) \
-    if (lanes == LN && vec == VC) return k_bucket_accum<T, D, LN, VC>;
-    if constexpr (sizeof(T) == 4) {
-        GCP_LG_SHAPES_F32(GCP_CASE)
-    } else {
-        GCP_LG_SHAPES_F64(GCP_CASE)
+    switch (order) {
+    case 3: return loss_grad_kernel<T, 3>(scatter, lanes, vec);
+    case 4: return loss_grad_kernel<T, 4>(scatter, lanes, vec);
+    case 5: return loss_grad_kernel<T, 5>(scatter, lanes, vec);
+    default: return loss_grad_kernel<T, 0>(scatter, lanes, vec);
     }
-#undef GCP_CASE
-    return nullptr;
 }
 
 template <typename T>
-static LGKernel<T> pick_kernel(int d, int src, int lanes, int vec)
+static BAKernel<T> pick_bucket_kernel(int order, int lanes, int vec)
 {
-    if (src >= 2) return pick_kernel_nonfused<T>(d, src, lanes, vec);
-    if (src == 0) {
-        if (d == 3) return pick_shape<T, 3, 0>(lanes, vec);
-        if (d == 4) return pick_shape<T, 4, 0>(lanes, vec);
-        return pick_shape<T, 0, 0>(lanes, vec);
+    switch (order) {
+    case 3: return bucket_kernel<T, 3>(lanes, vec);
+    case 4: return bucket_kernel<T, 4>(lanes, vec);
+    case 5: return bucket_kernel<T, 5>(lanes, vec);
+    default: return bucket_kernel<T, 0>(lanes, vec);
     }
-    if (d == 3) return pick_shape<T, 3, 1>(lanes, vec);
-    if (d == 4) return pick_shape<T, 4, 1>(lanes, vec);
-    return pick_shape<T, 0, 1>(lanes, vec);
-}
-
-template <typename T>
-static BAKernel<T> pick_bucket_kernel(int d, int lanes, int vec)
-{
-    if (d == 3) return pick_bucket_shape<T, 3>(lanes, vec);
-    if (d == 4) return pick_bucket_shape<T, 4>(lanes, vec);
-    return pick_bucket_shape<T, 0>(lanes, vec);
 }
 
 // Default lane shape.  Global float atomics are executed past the L2 at a
@@ -106,6 +101,12 @@ constexpr int kLdsPrivateBudget = 96 * 1024;    // bytes of private gradient per
 constexpr int kBucketLdsBudget = 32 * 1024;     // default bytes of one row block in LDS
 constexpr int kBucketMinSamples = 1 << 16;      // automatic bucketing only at or above this n
 constexpr int kMaxBuckets = 4096;
+// Small calls are cut into smaller chunks until there is one for this many
+// wavefronts per CU: with 64-sample chunks 2^15 samples of a 172x25000x300
+// tensor at rank 32 gave 512 wavefronts for 1024 SIMDs, each with 8 passes of
+// gather, evaluate and atomic adds one after the other (35 us); 8-sample
+// chunks take 22 us.
+constexpr int kWavesPerCu = 16;
 constexpr int kBucketWgPerCu = 8;              // owner-pass workgroups per CU aimed at
 
 template <typename T>
@@ -239,31 +240,44 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     if (R % vec != 0) return set_error(GCP_ERR_ARG, "vec = %d does not divide R = %d", vec, R);
     if (lanes * vec < R) return set_error(GCP_ERR_ARG, "lanes*vec = %d < R = %d", lanes * vec, R);
     const int src = write_y ? 2 : smp ? (given_values ? 3 : 1) : 0;
+    const int order = kernel_order(t, R, bucket_mask != 0);
     // the general-order float64 kernel with 64 lanes of one column needs 128
     // VGPRs and spills; even R takes 32 lanes of two columns instead
-    if (sizeof(T) == 8 && kernel_order(t) == 0 && lanes == 64 && vec == 1 && R % 2 == 0 && !(tile && tile->lanes > 0)) {
+    if (sizeof(T) == 8 && order == 0 && lanes == 64 && vec == 1 && R % 2 == 0 && !(tile && tile->lanes > 0)) {
         lanes = 32;
         vec = 2;
     }
-    LGKernel<T> kern = pick_kernel<T>(kernel_order(t), src, lanes, vec);
+    const bool scatter = !loss_only && bucket_mask != all_modes;
+    LGKernel<T> kern = pick_kernel<T>(order, scatter, lanes, vec);
     if (!kern) return set_error(GCP_ERR_UNSUPPORTED, "tile lanes = %d, vec = %d not built for this dtype", lanes, vec);
     const uintptr_t align = (uintptr_t)vec * sizeof(T);
     if (((uintptr_t)A % align) != 0) return set_error(GCP_ERR_ARG, "A is not %d-byte aligned", (int)align);
 
+    // 512 threads where workgroups sort (bucketed) or add their part of the
+    // objective: each such add waits its turn on the one address (11 ns)
     int block = 256;
     if (lds_mask) block = 1024;
-    else if (bucket_mask) block = 512;
+    else if (bucket_mask || (loss_out && !(xo && xo->loss_parts))) block = 512;
     if (tile && tile->block > 0) {
         if (tile->block % 64 != 0 || tile->block > 1024) return set_error(GCP_ERR_ARG, "block = %d", tile->block);
         block = tile->block;
     }
     const int nwaves = block / 64;
-    const int staging = nwaves * 64 * (8 + 2 * (int)sizeof(T));
-    size_t lds_bytes = (size_t)staging + (size_t)lds_elems * sizeof(T);
+    size_t lds_bytes = (size_t)lds_elems * sizeof(T);
     lds_bytes = (lds_bytes + 15) & ~(size_t)15;
     const int bucket_lds = (int)lds_bytes;
     if (bucket_mask) lds_bytes += (size_t)spb * (8 + sizeof(T)) + (size_t)nb * 8;
-    const int64_t nchunks = ceil_div(n, 64);
+    // samples per lane group and chunk: 64 samples a chunk, less while the
+    // call has too few of them to give kWavesPerCu wavefronts per CU one chunk
+    // each, down to what a lane group keeps in flight at once
+    const int groups = 64 / lanes;
+    int passes = lanes;
+    if (!bucket_mask)
+        while (passes > samples_in_flight(order, (int)sizeof(T), lanes, vec) &&
+               ceil_div(n, (int64_t)groups * passes) < (int64_t)kWavesPerCu * cus)
+            passes /= 2;
+    const int chunk = groups * passes;
+    const int64_t nchunks = ceil_div(n, chunk);
     int64_t grid;
     st = prepare_lds(reinterpret_cast<const void*>(kern), lds_bytes, t->device);
     if (st != GCP_OK) return st;
@@ -306,10 +320,12 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
         P.loss_parts = xo->loss_parts;
         if (xo->parts_used) *xo->parts_used = grid * nwaves;
     }
-    for (int k = 0; k < kMaxModes; ++k) P.rowoff[k] = k < d ? t->rowoff[k] : t->rowoff[d];
+    P.src = src;
+    P.passes = passes;
+    P.chunk_samples = chunk;
     P.lds_mask = lds_mask;
     P.lds_elems = lds_elems;
-    P.staging_bytes = staging;
+    set_row_offsets(P, t);
     P.bucket_mask = bucket_mask;
     P.n_bucket_modes = nbm;
     P.br_shift = br_shift;
@@ -338,7 +354,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(block), lds_bytes, stream, P);
     GCP_HIP(hipGetLastError());
     if (bucket_mask) {
-        BAKernel<T> bk = pick_bucket_kernel<T>(kernel_order(t), lanes, vec);
+        BAKernel<T> bk = pick_bucket_kernel<T>(order, lanes, vec);
         if (!bk) return set_error(GCP_ERR_UNSUPPORTED, "no bucket kernel for lanes = %d, vec = %d", lanes, vec);
         const int bblock = (tile && tile->bucket_block > 0) ? tile->bucket_block : 1024;
         if (bblock % 64 != 0 || bblock > 1024) return set_error(GCP_ERR_ARG, "bucket_block = %d", bblock);

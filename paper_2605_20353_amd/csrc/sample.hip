@@ -14,10 +14,9 @@ __global__ void __launch_bounds__(256) k_sample(SampleCtx<T> c, int64_t n, int64
     for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n; s += (int64_t)gridDim.x * blockDim.x) {
         uint64_t key;
         T x, w;
-        draw_sample<T, D>(c, c.step, s, key, x, w);
         constexpr int DM = D > 0 ? D : kMaxModes;
         uint32_t ci[DM];
-        unpack_all<D == 0>(c.L, dd, key, ci);
+        draw_sample<T, D>(c, c.step, s, key, ci, x, w);
 #pragma unroll
         for (int k = 0; k < DM; ++k)
             if (k < dd) coords[s * dd + k] = (int64_t)ci[k];
@@ -37,10 +36,9 @@ static gcp_status launch_sample(const gcp_tensor_s* t, const gcp_sample_params* 
     if (n == 0) return GCP_OK;
     if (!coords || !x || !w) return set_error(GCP_ERR_ARG, "output pointer is NULL");
     int64_t blocks = std::min<int64_t>(ceil_div(n, 256), (int64_t)device_cu_count(t->device) * 16);
-    const int order = kernel_order(t);
-    if (order == 3)
+    if (t->d == 3)
         k_sample<T, 3><<<(unsigned)blocks, 256, 0, stream>>>(c, n, coords, (T*)x, (T*)w);
-    else if (order == 4)
+    else if (t->d == 4)
         k_sample<T, 4><<<(unsigned)blocks, 256, 0, stream>>>(c, n, coords, (T*)x, (T*)w);
     else
         k_sample<T, 0><<<(unsigned)blocks, 256, 0, stream>>>(c, n, coords, (T*)x, (T*)w);

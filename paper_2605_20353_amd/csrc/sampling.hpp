@@ -43,48 +43,65 @@ struct SampleCtx {
     uint32_t* status;
 };
 
-// Fills the cell key, value and weight of sample s in [0, p + q) of
-// iteration `step` (the second Philox counter word).
+// Fills the cell key, coordinates, value and weight of sample s in [0, p + q)
+// of iteration `step` (the second Philox counter word).  Coordinates of drawn
+// cells come straight from the draw; only a stored nonzero's are unpacked.
+// The three streams share one generator call, so that the code holds its
+// forty wide multiplies once.
 template <typename T, int D>
-__device__ __forceinline__ void draw_sample(const SampleCtx<T>& c, uint64_t step, int64_t s, uint64_t& key, T& x,
-                                            T& w)
+__device__ __forceinline__ void draw_sample(const SampleCtx<T>& c, uint64_t step, int64_t s, uint64_t& key,
+                                            uint32_t (&ci)[D > 0 ? D : kMaxModes], T& x, T& w)
 {
-    if (c.kind == GCP_SAMPLE_UNIFORM) {
-        key = draw_cell_key<D>(c.L, c.d, c.seed, c.client, (uint64_t)s, step, kStreamUniform, 0);
-        int64_t lin = 0;
-        const int dd = D > 0 ? D : c.d;
-        constexpr int DM = D > 0 ? D : kMaxModes;
-        uint32_t ci[DM];
-        unpack_all<D == 0>(c.L, dd, key, ci);
+    constexpr int DM = D > 0 ? D : kMaxModes;
+    const int dd = D > 0 ? D : c.d;
+    const bool uniform = c.kind == GCP_SAMPLE_UNIFORM;
+    const bool nonzero = !uniform && s < c.p;
+    const uint64_t ctr = uniform || nonzero ? (uint64_t)s : (uint64_t)(s - c.p);
+    const uint64_t stream = uniform ? kStreamUniform : nonzero ? kStreamNonzero : kStreamZero;
+    for (int a = 0;; ++a) {
+        const U64x4 o = philox4x64_10(ctr, step, stream | ((uint64_t)a << 8), 0, c.seed, c.client);
+        if (nonzero) {
+            const int64_t j = (int64_t)range_map(o.v[0], (uint64_t)c.N);
+            // one 16-byte streaming load: records are touched once per draw
+            const u32x4 raw = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(c.rec + j));
+            key = (uint64_t)raw.x | ((uint64_t)raw.y << 32);
+            unpack_all<true>(c.L, dd, key, ci);
+            x = record_value<T>(raw);
+            w = c.w_nz;
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < (DM < 4 ? DM : 4); ++k)
+            if (k < dd) ci[k] = range_map32(o.v[k], (uint32_t)c.L.dims[k]);
+        if constexpr (DM > 4) {
+            if (dd > 4) {
+                const U64x4 o2 = philox4x64_10(ctr, step, stream | ((uint64_t)a << 8), 1, c.seed, c.client);
+#pragma unroll
+                for (int k = 4; k < DM; ++k)
+                    if (k < dd) ci[k] = range_map32(o2.v[k - 4], (uint32_t)c.L.dims[k]);
+            }
+        }
+        key = 0;
 #pragma unroll
         for (int k = 0; k < DM; ++k)
-            if (k < dd) lin += (int64_t)ci[k] * c.dense_stride[k];
-        x = c.dense[lin];
-        w = c.w_nz;
-        return;
-    }
-    if (s < c.p) {
-        U64x4 o = philox4x64_10((uint64_t)s, step, kStreamNonzero, 0, c.seed, c.client);
-        int64_t j = (int64_t)range_map(o.v[0], (uint64_t)c.N);
-        // one 16-byte streaming load: records are touched once per draw
-        u32x4 raw = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(c.rec + j));
-        key = (uint64_t)raw.x | ((uint64_t)raw.y << 32);
-        x = record_value<T>(raw);
-        w = c.w_nz;
-        return;
-    }
-    const uint64_t z = (uint64_t)(s - c.p);
-    const bool search = c.kind == GCP_SAMPLE_STRATIFIED;
-    for (int a = 0;; ++a) {
-        key = draw_cell_key<D>(c.L, c.d, c.seed, c.client, z, step, kStreamZero, (uint64_t)a);
-        if (!search || !table_contains(c.table, c.table_mask, c.table_log2, key)) break;
+            if (k < dd) key += pack_coord(c.L, (uint64_t)ci[k], k);
+        if (uniform) {
+            int64_t lin = 0;
+#pragma unroll
+            for (int k = 0; k < DM; ++k)
+                if (k < dd) lin += (int64_t)ci[k] * c.dense_stride[k];
+            x = c.dense[lin];
+            w = c.w_nz;
+            return;
+        }
+        x = T(0);
+        w = c.w_z;
+        if (c.kind != GCP_SAMPLE_STRATIFIED || !table_contains(c.table, c.table_mask, c.table_log2, key)) return;
         if (a + 1 >= c.max_attempts) {
             atomicOr(c.status, kStatusSampling);
-            break;
+            return;
         }
     }
-    x = T(0);
-    w = c.w_z;
 }
 
 }  // namespace gcp
