@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(1024) k_fed_sample(const FedArgs<T> F, int j)
 // for the block in LDS and stores the rows into G_c -- no other workgroup
 // writes them.
 template <typename T, int D, int LANES, int VEC>
-__global__ void __launch_bounds__(1024) k_fed_owner(const FedArgs<T> F)
+__global__ void __launch_bounds__(1024, (sizeof(T) == 4 && D > 0 ? 8 : 4)) k_fed_owner(const FedArgs<T> F)
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -253,8 +253,7 @@ __global__ void __launch_bounds__(1024) k_fed_owner(const FedArgs<T> F)
         }
     }
     T* part = reinterpret_cast<T*>(smem);
-    int* seg_cnt = reinterpret_cast<int*>(smem + ((((size_t)1 << P.br_shift) * P.R * sizeof(T) + 15) & ~(size_t)15));
-    bucket_accumulate<T, D, LANES, VEC>(P, k, rb, r0, rows, 0, P.nblocks, part, seg_cnt);
+    bucket_accumulate<T, D, LANES, VEC>(P, k, rb, r0, rows, 0, P.nblocks, part);
     T* dst = P.G + (roff + r0) * P.R;
     for (int64_t e = threadIdx.x; e < rows * P.R; e += blockDim.x) dst[e] = part[e];
 }
@@ -407,6 +406,7 @@ struct gcp_fed_s {
     const void* sample_kernel = nullptr;
     const void* owner_kernel = nullptr;
     size_t sample_lds = 0, owner_lds = 0;
+    int owner_block = 1024;        // threads of an owner workgroup
     int nb_max = 0;                // row blocks of the largest client
     int64_t max_params = 0;        // parameters of the largest client
     hipGraph_t graph = nullptr;
@@ -497,8 +497,8 @@ static gcp_status fed_build(gcp_fed_s* f)
             for (int k = 0; k < d; ++k)
                 if ((bucket_mask >> k) & 1u) nb_c[c] += (int)ceil_div(t->dims[k], int64_t(1) << br_shift);
             nb_max = std::max(nb_max, nb_c[c]);
-            // entries, then counts and starts, 16-byte aligned per client
-            const int64_t bytes = nblocks_c * spb * nbm * 16 + (((int64_t)2 * nb_c[c] * nblocks_c * 4 + 15) & ~int64_t(15));
+            // entries, then the bucket starts, 16-byte aligned per client
+            const int64_t bytes = nblocks_c * spb * nbm * 16 + (((int64_t)(nb_c[c] + 1) * nblocks_c * 4 + 15) & ~int64_t(15));
             ws_off[c + 1] = ws_off[c] + bytes;
         }
         GCP_HIP(hipMalloc(&f->bucket_ws, (size_t)std::max<int64_t>(16, ws_off[K])));
@@ -506,8 +506,8 @@ static gcp_status fed_build(gcp_fed_s* f)
         f->bucket_mask = bucket_mask;
         f->spb = spb;
         f->nb_max = nb_max;
-        f->sample_lds = ((f->lds_bytes + 15) & ~(size_t)15) + (size_t)spb * (8 + sizeof(T)) + (size_t)nb_max * 8;
-        f->owner_lds = ((((size_t)1 << br_shift) * R * sizeof(T) + 15) & ~(size_t)15) + (size_t)nblocks_c * 8;
+        f->sample_lds = ((f->lds_bytes + 15) & ~(size_t)15) + sort_lds_bytes(spb, (int)sizeof(T), nb_max);
+        f->owner_lds = (((size_t)1 << br_shift) * R * sizeof(T) + 15) & ~(size_t)15;
     }
     for (int c = 0; c < K; ++c) {
         const gcp_fed_client& cl = f->clients[c];
@@ -558,8 +558,7 @@ static gcp_status fed_build(gcp_fed_s* f)
             for (int k = d; k <= kMaxModes; ++k) h.P.bucket_base[k] = nb;
             unsigned char* base = (unsigned char*)f->bucket_ws + ws_off[c];
             h.P.entries = (uint4*)base;
-            h.P.hist = (int*)(base + nblocks_c * spb * nbm * 16);
-            h.P.start = h.P.hist + (int64_t)nb_c[c] * nblocks_c;
+            h.P.start = (int*)(base + nblocks_c * spb * nbm * 16);
         }
         h.B = (T*)cl.B;
         h.C = (T*)cl.C;
@@ -644,6 +643,17 @@ static gcp_status fed_build(gcp_fed_s* f)
         if (st != GCP_OK) return st;
         st = prepare_lds(f->owner_kernel, f->owner_lds, f->device);
         if (st != GCP_OK) return st;
+        // owner workgroups: 1024 threads, fewer when that lets all of them start
+        // at once (16 clients of 5000 x 5000 x 500 blocks: 640 workgroups on
+        // 512 places leave a second, nearly empty wave)
+        for (int threads = 1024; threads >= 256; threads /= 2) {
+            int per_cu = 0;
+            GCP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f->owner_kernel, threads, f->owner_lds));
+            if ((int64_t)K * f->nb_max <= (int64_t)per_cu * device_cu_count(f->device)) {
+                f->owner_block = threads;
+                break;
+            }
+        }
         if (D.workgroups_per_client <= 0) {
             // automatic: the sampling launch fills the GPU once
             int per_cu = 0;
@@ -702,7 +712,7 @@ static gcp_status fed_launch_batched(gcp_fed_s* f, hipStream_t stream)
                                dim3((unsigned)f->W, K), dim3(f->block), f->sample_lds, stream, a, j);
             GCP_HIP(hipGetLastError());
             hipLaunchKernelGGL(reinterpret_cast<FedKernel<T>>(const_cast<void*>(f->owner_kernel)),
-                               dim3((unsigned)f->nb_max, K), dim3(1024), f->owner_lds, stream, a);
+                               dim3((unsigned)f->nb_max, K), dim3(f->owner_block), f->owner_lds, stream, a);
             GCP_HIP(hipGetLastError());
             k_fed_adam<T><<<dim3(ab, K), 256, 0, stream>>>(a, j);
             GCP_HIP(hipGetLastError());

@@ -77,7 +77,7 @@ struct gcp_tensor_s {
     // workspace of the bucketed scatter (gcp_tensor_reserve)
     void* ws = nullptr;
     int64_t ws_entries = 0;            // 16-byte sample entries
-    int64_t ws_hist = 0;               // ints in each of the count and start arrays
+    int64_t ws_starts = 0;             // ints for the workgroups' bucket starts
     int64_t ws_bytes = 0;
     int64_t ws_max_samples = 0;        // samples per call the workspace was sized for
 };
@@ -330,14 +330,14 @@ int64_t ceil_div(int64_t a, int64_t b);
 gcp_status prepare_lds(const void* fn, size_t bytes, int device);
 
 // Device memory the row-bucketed scatter of gcp_loss_grad may use for its
-// sample entries and per-(row block, workgroup) counts and starts.  Either a
-// reservation of gcp_tensor_reserve (entries / hist / max_samples fixed when
+// sample entries and each workgroup's bucket starts.  Either a
+// reservation of gcp_tensor_reserve (entries / starts / max_samples fixed when
 // it was sized) or, when scratch_bytes > 0, a fixed scratch region of that
 // many bytes carved up afresh by each call.
 struct LGWorkspace {
     void* base = nullptr;
     int64_t entries = 0;        // reservation: 16-byte entries
-    int64_t hist = 0;           // reservation: ints in each of counts and starts
+    int64_t starts = 0;         // reservation: ints for the workgroups' bucket starts
     int64_t max_samples = 0;    // reservation: p + q it was sized for
     int64_t scratch_bytes = 0;  // > 0: fixed scratch region of this size
 };

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
 
 #include "sampling.hpp"
 
@@ -45,8 +46,7 @@ struct LGParams {
     int64_t entry_cap;         // entries per workgroup segment list = spb * n_bucket_modes
     int bucket_lds;            // byte offset of the bucket staging in LDS
     uint4* entries;            // [J][entry_cap] 16-byte {key, y}
-    int* hist;                 // [nb][J] entries per (bucket, workgroup)
-    int* start;                // [nb][J] first entry of the bucket in the workgroup's list
+    int* start;                // [J][nb + 1] first entry of each bucket in the workgroup's list, then their number
     // owner pass: mode k's row blocks use workgroups [bwg_base[k], bwg_base[k+1]),
     // bsplits[k] per row block, each reading bsegs[k] consecutive segments
     int64_t bwg_base[kMaxModes + 1];
@@ -288,7 +288,7 @@ __device__ __forceinline__ T sample_y(const LGParams<T>& P, T x, T w, T m, bool 
     return y;
 }
 
-// Exclusive prefix sum of cnt[0, n) into off[0, n) by one wavefront.
+// Exclusive prefix sum of cnt[0, n) into off[0, n] by one wavefront.
 __device__ inline void wave_exclusive_scan(const int* cnt, int* off, int n, int lane)
 {
     const int per = (n + 63) / 64;
@@ -309,6 +309,7 @@ __device__ inline void wave_exclusive_scan(const int* cnt, int* off, int n, int 
             run += cnt[b0 + i];
         }
     }
+    if (lane == 63) off[n] = incl;
 }
 
 // Samples per lane group whose factor-row gathers are issued together; divides
@@ -559,16 +560,16 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
 }
 
 // Bucketed scatter, sampling side: sorts the (key, y) of the workgroup's
-// nvalid staged samples (bkey, by in LDS) by (mode, row block) into segment
-// list `seg` of the bucket workspace -- count, scan, place -- and records the
-// list's per-bucket counts and starts.  Every thread of the workgroup calls it.
+// nvalid staged samples (bkey, by in LDS) by (mode, bucket) into segment
+// list `seg` of the bucket workspace -- count, scan, place -- and records
+// where each bucket starts in the list.  bcnt is LDS scratch of nb ints, boff
+// of nb + 1.  Every thread of the workgroup calls it.
 template <typename T, int D>
 __device__ __forceinline__ void bucket_write_out(const LGParams<T>& P, int64_t seg, int nvalid, const uint64_t* bkey,
                                                  const T* by, int* bcnt, int* boff)
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
     const int dd = D > 0 ? D : P.sc.d;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     __syncthreads();
     for (int b = threadIdx.x; b < P.nb; b += blockDim.x) bcnt[b] = 0;
     __syncthreads();
@@ -577,15 +578,14 @@ __device__ __forceinline__ void bucket_write_out(const LGParams<T>& P, int64_t s
         unpack_all<D == 0>(P.sc.L, dd, bkey[e], ci);
 #pragma unroll
         for (int k = 0; k < DM; ++k)
-            if (k < dd && ((P.bucket_mask >> k) & 1u)) atomicAdd(bcnt + P.bucket_base[k] + (int)(ci[k] >> P.br_shift), 1);
+            if (k < dd && ((P.bucket_mask >> k) & 1u))
+                atomicAdd(bcnt + P.bucket_base[k] + (int)(ci[k] >> P.br_shift), 1);
     }
     __syncthreads();
-    if (wave == 0) wave_exclusive_scan(bcnt, boff, P.nb, lane);
+    if ((threadIdx.x >> 6) == 0) wave_exclusive_scan(bcnt, boff, P.nb, threadIdx.x);
     __syncthreads();
-    for (int b = threadIdx.x; b < P.nb; b += blockDim.x) {
-        P.hist[(int64_t)b * P.nblocks + seg] = bcnt[b];
-        P.start[(int64_t)b * P.nblocks + seg] = boff[b];
-    }
+    int* start = P.start + seg * (P.nb + 1);
+    for (int b = threadIdx.x; b <= P.nb; b += blockDim.x) start[b] = boff[b];
     __syncthreads();
     uint4* out = P.entries + seg * P.entry_cap;
     for (int e = threadIdx.x; e < nvalid; e += blockDim.x) {
@@ -604,180 +604,182 @@ __device__ __forceinline__ void bucket_write_out(const LGParams<T>& P, int64_t s
     __syncthreads();
 }
 
+// LDS of the sort: the staged samples, the buckets' counts and offsets.
+inline size_t sort_lds_bytes(int spb, int elem_bytes, int nb) { return (size_t)spb * (8 + elem_bytes) + (size_t)nb * 8 + 4; }
+
+// Value that lane IT of each lane group (LANES lanes) holds, in every lane of
+// the group: DPP row broadcasts, one per group of a row of 16 lanes, each
+// written to its group's banks of four lanes; a bpermute for other widths.
+template <int LANES, int IT>
+__device__ __forceinline__ uint32_t group_bcast(uint32_t v, int group_at)
+{
+    if constexpr (LANES == 16) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + IT, 0xf, 0xf, true);
+    } else if constexpr (LANES == 8) {
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x150 + IT, 0xf, 0xf, true);
+        return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)v, 0x158 + IT, 0xf, 0xc, false);
+    } else if constexpr (LANES == 4) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, IT * 0x55, 0xf, 0xf, true);    // quad_perm
+    } else {
+        return (uint32_t)__builtin_amdgcn_ds_bpermute(group_at + (IT << 2), (int)v);
+    }
+}
+template <int LANES, int IT>
+__device__ __forceinline__ float group_bcast(float v, int group_at)
+{
+    return __uint_as_float(group_bcast<LANES, IT>(__float_as_uint(v), group_at));
+}
+template <int LANES, int IT>
+__device__ __forceinline__ double group_bcast(double v, int group_at)
+{
+    return __hiloint2double((int)group_bcast<LANES, IT>((uint32_t)__double2hiint(v), group_at),
+                            (int)group_bcast<LANES, IT>((uint32_t)__double2loint(v), group_at));
+}
+
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(static_cast<F&&>(f));
+    }
+}
+
 // Bucketed scatter, owner side: accumulates into `part` (LDS, rows x R) the
 // contributions y prod_{n != k} A_n[i_n, :] of every entry of bucket b (rows
-// [r0, r0 + rows) of mode k) in segment lists [j0, j1).  Each wave takes whole
-// segments in turn, loading the next pass's entries while it gathers the
-// other modes' rows; adds go through LDS compare-and-swap.  seg_cnt is LDS
-// scratch for 2 (j1 - j0) ints.  Every thread of the workgroup calls it; part
-// is complete when it returns.
+// [r0, r0 + rows) of mode k) in segment lists [j0, j1).  Each wavefront takes a
+// run of consecutive segments and reads them as one stream of entries, 64 at a
+// time, one entry per lane (a binary search over the segments' running counts
+// finds a lane's entry, so that short segments fill whole batches too).  The
+// lane unpacks its entry once -- the other modes' row offsets, its row's place
+// in `part`, y -- and its lane group takes it by DPP broadcasts, gathers the
+// rows and adds the products to LDS by compare-and-swap.  (An entry read by all
+// lanes of its group costs the vector memory path as many cycles as a row
+// gather, its unpacking in all of them as many instructions as the products,
+// and a broadcast by bpermute adds to the LDS, which the adds fill.)  The next
+// batch's entries are in flight while a batch is worked on.  Every thread of
+// the workgroup calls it; part is complete when it returns.
 template <typename T, int D, int LANES, int VEC>
 __device__ __forceinline__ void bucket_accumulate(const LGParams<T>& P, int k, int b, int64_t r0, int64_t rows,
-                                                  int64_t j0, int64_t j1, T* part, int* seg_cnt)
+                                                  int64_t j0, int64_t j1, T* part)
 {
     constexpr int S = 64 / LANES;
     constexpr int U = owner_in_flight<T, D, LANES, VEC>();
     constexpr int DM = D > 0 ? D : kMaxModes;
-    static_assert(VEC == 1 || VEC == 2 || VEC == 4, "columns per lane");
+    constexpr int DO = DM - 1;
+    static_assert(D == 0 || D >= 2, "orders with their own kernels");
     const int nwaves = blockDim.x >> 6;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane / LANES, cl = lane % LANES;
+    const int group_at = (lane & ~(LANES - 1)) << 2;
     const int col0 = cl * VEC;
     const int R = P.R;
     const bool col_ok = col0 < R;
+    const int colL = col_ok ? col0 : 0;
+    const uint32_t colb = (uint32_t)colL * (uint32_t)sizeof(T);
     const int dd = D > 0 ? D : P.sc.d;
-    // mode k's key field, selected with compile-time indices: a run-time
-    // index into the parameter block would force a register copy of it
-    // (the persistent FedAdam kernel holds one) out to scratch memory
-    int shift_k = 0;
-    uint64_t mask_k = 0;
-#pragma unroll
-    for (int kk = 0; kk < DM; ++kk)
-        if (kk == k) {
-            shift_k = P.sc.L.shift[kk];
-            mask_k = P.sc.L.mask[kk];
-        }
-    int* seg_start = seg_cnt + (j1 - j0);
+    // entry of the batch at t this lane holds: a full batch in lane order (one
+    // coalesced read, pass it works on lane it of every group), the last one
+    // spread over the groups so that it takes as few passes as it can
+    auto hold = [&](int t, int total) { return t + (t + 64 <= total ? lane : cl * S + g); };
     for (int64_t e = threadIdx.x; e < rows * R; e += blockDim.x) part[e] = T(0);
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += blockDim.x) {
-        seg_cnt[j - j0] = P.hist[(int64_t)b * P.nblocks + j];
-        seg_start[j - j0] = P.start[(int64_t)b * P.nblocks + j];
-    }
     __syncthreads();
 
-    if constexpr (D > 0) {
-        // Bit-packed keys: every load below is unconditional.  The D - 1 modes
-        // other than k are enumerated at compile time (shift, mask, row offset
-        // picked with compile-time indices), lanes past column R read column 0
-        // and lanes past the segment's end re-read its last entry, so each load
-        // has an in-bounds address and no branch around it.  Loads under a
-        // branch make the compiler wait for all outstanding loads before each
-        // one, which serialises the gathers of a pass.
-        static_assert(D >= 2, "orders with their own kernels");
-        constexpr int DO = D - 1;
-        int sh_o[DO];
-        uint32_t mk_o[DO], ro_o[DO];
+    const int per = ((int)(j1 - j0) + nwaves - 1) / nwaves;
+    const int64_t je = std::min<int64_t>(j0 + (wave + 1) * per, j1);
+    for (int64_t jc = j0 + wave * per; jc < je; jc += 64) {
+        // lane i: segment jc + i, its count, the entries before it in this
+        // run, and where entry 0 of the stream would be if the stream began
+        // inside this segment
+        const bool has = jc + lane < je;
+        const int* st = P.start + (jc + lane) * (P.nb + 1) + b;
+        const int first = has ? st[0] : 0;
+        const int cnt = has ? st[1] - first : 0;
+        int incl = cnt;
 #pragma unroll
-        for (int o = 0; o < DO; ++o) {
-            const int m = o + (o >= k ? 1 : 0);
-            sh_o[o] = 0;
-            mk_o[o] = 0;
-            ro_o[o] = 0;
-#pragma unroll
-            for (int kk = 0; kk < D; ++kk)
-                if (kk == m) {
-                    sh_o[o] = P.sc.L.shift[kk];
-                    mk_o[o] = (uint32_t)P.sc.L.mask[kk];
-                    ro_o[o] = (uint32_t)P.rowoff[kk];
-                }
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += o;
         }
-        const int colL = col_ok ? col0 : 0;
-        for (int64_t j = j0 + wave; j < j1; j += nwaves) {
-            const int cnt = seg_cnt[j - j0];
-            if (cnt == 0) continue;
-            const uint4* seg = P.entries + j * P.entry_cap + seg_start[j - j0];
-            uint4 nxt[U];
+        const int excl = incl - cnt;
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (total == 0) continue;
+        const int rel = lane * (int)P.entry_cap + first - excl;
+        const uint4* base = P.entries + jc * P.entry_cap;
+        auto entry_of = [&](int e) -> uint4 {          // entry min(e, total - 1) of the stream
+            e = min(e, total - 1);
+            int sg = 0;                                // last segment that begins at or before e
 #pragma unroll
-            for (int u = 0; u < U; ++u) nxt[u] = seg[min(u * S + g, cnt - 1)];
-            for (int base = 0; base < cnt; base += S * U) {
-                uint64_t key[U];
-                T y[U];
-                T a[U][DO][VEC];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    key[u] = (uint64_t)nxt[u].x | ((uint64_t)nxt[u].y << 32);
-                    y[u] = entry_y<T>(nxt[u]);
-#pragma unroll
-                    for (int o = 0; o < DO; ++o) {
-                        const uint32_t row = ro_o[o] + ((uint32_t)(key[u] >> sh_o[o]) & mk_o[o]);
-                        load_cols<T, VEC>(P.A + row_elem(row, R) + colL, a[u][o]);
-                    }
-                }
-                // the next pass's entries stay in flight through this pass's
-                // scatter
-#pragma unroll
-                for (int u = 0; u < U; ++u) nxt[u] = seg[min(base + S * U + u * S + g, cnt - 1)];
-                // keeps the gathers here: sunk into the scatter branch below
-                // they would issue after the prefetch, and waiting for them
-                // would wait for the prefetch as well
-                __asm__ volatile("" ::: "memory");
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (base + u * S + g >= cnt || !col_ok) continue;
-                    const uint32_t i = (uint32_t)((key[u] >> shift_k) & mask_k) - (uint32_t)r0;
-                    T c[VEC];
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) {
-                        c[v] = y[u];
-#pragma unroll
-                        for (int o = 0; o < DO; ++o) c[v] *= a[u][o][v];
-                    }
-                    lds_add_cols<T, VEC>(part + i * (uint32_t)R + col0, c);
-                }
+            for (int step = 32; step >= 1; step >>= 1) {
+                const int at = __builtin_amdgcn_ds_bpermute((sg + step) << 2, excl);
+                if (at <= e) sg += step;
             }
-        }
-        __syncthreads();
-        return;
-    }
-    // General order (run-time d, either key form), with the loads as
-    // unconditional as above: the d - 1 modes other than k fill slots
-    // 0 .. d - 2 in mode order (slot o holds mode o, or o + 1 from k on, both
-    // compile-time indices), slots past d - 2 re-read column block 0 of the
-    // first model row and count as ones, lanes past column R read column 0,
-    // and lanes past the segment's end re-read its last entry.
-    constexpr int SO = DM - 1;
-    const int colL = col_ok ? col0 : 0;
-    for (int64_t j = j0 + wave; j < j1; j += nwaves) {
-        const int cnt = seg_cnt[j - j0];
-        if (cnt == 0) continue;
-        const uint4* seg = P.entries + j * P.entry_cap + seg_start[j - j0];
-        // entries of the next pass are loaded while this pass gathers rows
-        uint4 nxt[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) nxt[u] = seg[min(u * S + g, cnt - 1)];
-        for (int base = 0; base < cnt; base += S * U) {
-            uint32_t ik[U];
-            T y[U];
-            T a[U][SO][VEC];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint4 ent = nxt[u];
-                const uint64_t key = (uint64_t)ent.x | ((uint64_t)ent.y << 32);
+            return base[e + __builtin_amdgcn_ds_bpermute(sg << 2, rel)];
+        };
+        uint4 nxt = entry_of(hold(0, total));
+        for (int t = 0; t < total; t += 64) {
+            const int nb = min(64, total - t);
+            const uint64_t key = (uint64_t)nxt.x | ((uint64_t)nxt.y << 32);
+            const T y = entry_y<T>(nxt);
+            uint32_t off[DO];                          // D > 0: byte offset of the row in A; else its row index
+            uint32_t loc;                              // byte offset of the entry's row in part
+            {
                 uint32_t ci[DM];
-                unpack_all<true>(P.sc.L, dd, key, ci);
-                // the owned mode's row, picked with compile-time indices
-                ik[u] = ci[0];
+                unpack_all<D == 0>(P.sc.L, dd, key, ci);
+                uint32_t ik = ci[0];
 #pragma unroll
                 for (int kk = 1; kk < DM; ++kk)
-                    if (kk == k) ik[u] = ci[kk];
-                y[u] = entry_y<T>(ent);
+                    if (kk == k) ik = ci[kk];
+                loc = (ik - (uint32_t)r0) * P.stride_b;
+                // slot o holds mode o, or o + 1 from k on
 #pragma unroll
-                for (int o = 0; o < SO; ++o) {
+                for (int o = 0; o < DO; ++o) {
                     const bool after = o >= k;
-                    const uint64_t row = after ? (uint64_t)P.rowoff[o + 1] + ci[o + 1] : (uint64_t)P.rowoff[o] + ci[o];
-                    const T* src = P.A + (o < dd - 1 ? row_elem(row, R) : 0) + colL;
-                    load_cols<T, VEC>(src, a[u][o]);
+                    const uint32_t i = after ? ci[o + 1] : ci[o];
+                    if constexpr (D > 0) off[o] = (after ? P.rowb[o + 1] : P.rowb[o]) + i * P.stride_b;
+                    else off[o] = (uint32_t)(after ? P.rowoff[o + 1] : P.rowoff[o]) + i;
                 }
             }
-            // the next pass's entries stay in flight through this pass's
-            // scatter
+            static_for<LANES / U>([&](auto pp) {
+                constexpr int it0 = decltype(pp)::value * U;
+                if (it0 * S < nb) {
+                    T a[U][DO][VEC];
+                    static_for<U>([&](auto uu) {
+                        constexpr int u = decltype(uu)::value;
 #pragma unroll
-            for (int u = 0; u < U; ++u) nxt[u] = seg[min(base + S * U + u * S + g, cnt - 1)];
-            __asm__ volatile("" ::: "memory");
+                        for (int o = 0; o < DO; ++o) {
+                            if (D > 0 || o < dd - 1) {
+                                const uint32_t ro = group_bcast<LANES, it0 + u>(off[o], group_at);
+                                if constexpr (D > 0)
+                                    load_cols<T, VEC>(reinterpret_cast<const T*>(
+                                                          reinterpret_cast<const char*>(P.A) + (ro + colb)),
+                                                      a[u][o]);
+                                else
+                                    load_cols<T, VEC>(P.A + row_elem(ro, R) + colL, a[u][o]);
+                            }
+                        }
+                    });
+                    // the next batch's entries, behind the first gathers (loads
+                    // return in order)
+                    if (it0 == 0 && t + 64 < total) nxt = entry_of(hold(t + 64, total));
+                    static_for<U>([&](auto uu) {
+                        constexpr int u = decltype(uu)::value;
+                        const T yu = group_bcast<LANES, it0 + u>(y, group_at);
+                        const uint32_t lu = group_bcast<LANES, it0 + u>(loc, group_at);
+                        if ((nb == 64 || (it0 + u) * S + g < nb) && col_ok) {
+                            T c[VEC];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (base + u * S + g >= cnt || !col_ok) continue;
-                const uint32_t i = ik[u] - (uint32_t)r0;
-                T c[VEC];
+                            for (int v = 0; v < VEC; ++v) {
+                                c[v] = yu;
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    c[v] = y[u];
-#pragma unroll
-                    for (int o = 0; o < SO; ++o)
-                        if (o < dd - 1) c[v] *= a[u][o][v];
+                                for (int o = 0; o < DO; ++o)
+                                    if (D > 0 || o < dd - 1) c[v] *= a[u][o][v];
+                            }
+                            lds_add_cols<T, VEC>(reinterpret_cast<T*>(reinterpret_cast<char*>(part) + (lu + colb)), c);
+                        }
+                    });
                 }
-                lds_add_cols<T, VEC>(part + i * (uint32_t)R + col0, c);
-            }
+            });
         }
     }
     __syncthreads();

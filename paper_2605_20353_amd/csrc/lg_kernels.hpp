@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_
 // modes' rows, forms y prod_{n != k} A_n[i_n, :] and adds it to the LDS copy
 // of its rows; the block is flushed to G once.
 template <typename T, int D, int LANES, int VEC>
-__global__ void __launch_bounds__(1024) k_bucket_accum(const LGParams<T> P)
+__global__ void __launch_bounds__(1024, (sizeof(T) == 4 && D > 0 ? 8 : 4)) k_bucket_accum(const LGParams<T> P)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T* part = reinterpret_cast<T*>(smem);
@@ -124,8 +124,8 @@ __global__ void __launch_bounds__(1024) k_bucket_accum(const LGParams<T> P)
     int k = 0;
     for (int kk = 0; kk < dd; ++kk)
         if (P.bwg_base[kk] <= (int64_t)blockIdx.x && (int64_t)blockIdx.x < P.bwg_base[kk + 1]) k = kk;
-    const int splits = P.bsplits[k];
-    const int64_t local = (int64_t)blockIdx.x - P.bwg_base[k];
+    const uint32_t splits = (uint32_t)P.bsplits[k];
+    const uint32_t local = blockIdx.x - (uint32_t)P.bwg_base[k];
     const int b = P.bucket_base[k] + (int)(local / splits);
     const int split = (int)(local % splits);
     const int64_t r0 = (int64_t)(b - P.bucket_base[k]) << P.br_shift;
@@ -134,9 +134,7 @@ __global__ void __launch_bounds__(1024) k_bucket_accum(const LGParams<T> P)
     // waves per workgroup); the last split takes the remainder
     const int64_t j0 = (int64_t)split * P.bsegs[k];
     const int64_t j1 = std::min<int64_t>(P.nblocks, j0 + P.bsegs[k]);
-    int* seg_cnt = reinterpret_cast<int*>(smem + (((size_t)rows * R * sizeof(T) + 15) & ~(size_t)15));
-    bucket_accumulate<T, D, LANES, VEC>(P, k, b, r0, rows, j0, j1, part, seg_cnt);
-    __syncthreads();
+    bucket_accumulate<T, D, LANES, VEC>(P, k, b, r0, rows, j0, j1, part);
     T* dst = P.G + (P.rowoff[k] + r0) * R;
     for (int64_t e = threadIdx.x; e < rows * R; e += blockDim.x) {
         const T v = part[e];

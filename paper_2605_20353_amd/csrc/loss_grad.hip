@@ -204,8 +204,8 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
         nblocks = ceil_div(n, spb);
         if (!ws.base) return set_error(GCP_ERR_ARG, "bucketed scatter needs gcp_tensor_reserve first");
         if (ws.scratch_bytes > 0) {
-            // fixed scratch: entries first, then counts and starts
-            const int64_t need = nblocks * spb * (int64_t)nbm * 16 + (int64_t)nb * nblocks * 8;
+            // fixed scratch: entries first, then the bucket starts
+            const int64_t need = nblocks * spb * (int64_t)nbm * 16 + (int64_t)(nb + 1) * nblocks * 4;
             if (need > ws.scratch_bytes) {
                 if (req_bucket >= 0)
                     return set_error(GCP_ERR_ARG,
@@ -216,7 +216,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
                 nb = nbm = spb = 0;
                 nblocks = 0;
             }
-        } else if (n > ws.max_samples || nblocks * spb * (int64_t)nbm > ws.entries || (int64_t)nb * nblocks > ws.hist) {
+        } else if (n > ws.max_samples || nblocks * spb * (int64_t)nbm > ws.entries || (int64_t)(nb + 1) * nblocks > ws.starts) {
             return set_error(GCP_ERR_ARG, "workspace reserved by gcp_tensor_reserve is too small for this call");
         }
     }
@@ -266,7 +266,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     size_t lds_bytes = (size_t)lds_elems * sizeof(T);
     lds_bytes = (lds_bytes + 15) & ~(size_t)15;
     const int bucket_lds = (int)lds_bytes;
-    if (bucket_mask) lds_bytes += (size_t)spb * (8 + sizeof(T)) + (size_t)nb * 8;
+    if (bucket_mask) lds_bytes += sort_lds_bytes(spb, (int)sizeof(T), nb);
     // samples per lane group and chunk: 64 samples a chunk, less while the
     // call has too few of them to give kWavesPerCu wavefronts per CU one chunk
     // each, down to what a lane group keeps in flight at once
@@ -335,11 +335,8 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     P.entry_cap = (int64_t)spb * nbm;
     P.bucket_lds = bucket_lds;
     if (bucket_mask) {
-        const int64_t ent = ws.scratch_bytes > 0 ? nblocks * spb * (int64_t)nbm : ws.entries;
-        const int64_t hist = ws.scratch_bytes > 0 ? (int64_t)nb * nblocks : ws.hist;
         P.entries = (uint4*)ws.base;
-        P.hist = (int*)((char*)ws.base + ent * 16);
-        P.start = P.hist + hist;
+        P.start = (int*)((char*)ws.base + nblocks * spb * (int64_t)nbm * 16);
     }
 
     if (!accumulate) {
@@ -370,7 +367,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
         for (int k = 0; k < d; ++k)
             if ((bucket_mask >> k) & 1u) expect_total += (double)n;
         const double per_wg = std::max(1.0, expect_total / ((double)kBucketWgPerCu * cus));
-        int64_t wg = 0, max_segs = 0;
+        int64_t wg = 0;
         for (int k = 0; k < d; ++k) {
             P.bwg_base[k] = wg;
             P.bsplits[k] = 1;
@@ -388,11 +385,10 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
             segs = std::max<int64_t>(1, std::min<int64_t>(segs, nblocks));
             P.bsegs[k] = (int)segs;
             P.bsplits[k] = (int)ceil_div(nblocks, segs);
-            max_segs = std::max<int64_t>(max_segs, segs);
             wg += (int64_t)(P.bucket_base[k + 1] - P.bucket_base[k]) * P.bsplits[k];
         }
         for (int k = d; k <= kMaxModes; ++k) P.bwg_base[k] = wg;
-        const size_t part_bytes = ((((size_t)1 << br_shift) * R * sizeof(T) + 15) & ~(size_t)15) + 8 * (size_t)max_segs;
+        const size_t part_bytes = (((size_t)1 << br_shift) * R * sizeof(T) + 15) & ~(size_t)15;
         st = prepare_lds(reinterpret_cast<const void*>(bk), part_bytes, t->device);
         if (st != GCP_OK) return st;
         hipLaunchKernelGGL(bk, dim3((unsigned)wg), dim3(bblock), part_bytes, stream, P);
@@ -418,7 +414,7 @@ static LGWorkspace reserved_workspace(const gcp_tensor_s* t)
     LGWorkspace ws;
     ws.base = t->ws;
     ws.entries = t->ws_entries;
-    ws.hist = t->ws_hist;
+    ws.starts = t->ws_starts;
     ws.max_samples = t->ws_max_samples;
     return ws;
 }

@@ -303,7 +303,7 @@ gcp_status gcp_tensor_reserve(gcp_tensor t, int64_t max_samples, int R, hipStrea
     if (t->ws) {
         GCP_HIP(hipFree(t->ws));
         t->ws = nullptr;
-        t->ws_entries = t->ws_hist = t->ws_bytes = t->ws_max_samples = 0;
+        t->ws_entries = t->ws_starts = t->ws_bytes = t->ws_max_samples = 0;
     }
     if (max_samples == 0) { GCP_HIP(hipSetDevice(cur)); return GCP_OK; }
     // smallest row block: 8 KiB of LDS; fewest samples per workgroup: 512
@@ -315,10 +315,10 @@ gcp_status gcp_tensor_reserve(gcp_tensor t, int64_t max_samples, int R, hipStrea
     nb = std::min<int64_t>(nb, 4096);
     const int64_t nblocks = ceil_div(max_samples, 512);
     const int64_t entries = (max_samples + 8192) * t->d;
-    const int64_t hist = nb * nblocks;
+    const int64_t starts = 2 * nb * nblocks;
     // the same region serves GCP_DETERMINISTIC calls
     const int64_t det = max_samples < (int64_t(1) << 32) ? det_workspace_bytes(t, max_samples) : 0;
-    const int64_t bytes = std::max<int64_t>(entries * 16 + hist * 8, det);
+    const int64_t bytes = std::max<int64_t>(entries * 16 + starts * 4, det);
     hipError_t e = hipMalloc(&t->ws, (size_t)bytes);
     if (e != hipSuccess) {
         t->ws = nullptr;
@@ -326,7 +326,7 @@ gcp_status gcp_tensor_reserve(gcp_tensor t, int64_t max_samples, int R, hipStrea
         return hip_error(e, "hipMalloc(workspace)");
     }
     t->ws_entries = entries;
-    t->ws_hist = hist;
+    t->ws_starts = starts;
     t->ws_bytes = bytes;
     t->ws_max_samples = max_samples;
     GCP_HIP(hipSetDevice(cur));
