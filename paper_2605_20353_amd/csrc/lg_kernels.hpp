@@ -41,32 +41,36 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_
     const int R = P.R;
     const T scale = P.scale ? *P.scale : T(1);
     const bool tiled = P.bucket_mask != 0;
-    const int64_t block_s0 = tiled ? (int64_t)blockIdx.x * P.spb : 0;
     double lacc = 0.0;
 
-    // tiled launches give workgroup j the samples [j*spb, (j+1)*spb)
-    const int cs = P.chunk_samples;
-    int64_t s0, s_end, s_step;
-    if (tiled) {
-        s0 = block_s0 + (int64_t)wave * cs;
-        s_end = std::min<int64_t>(P.n, block_s0 + P.spb);
-        s_step = (int64_t)nwaves * cs;
-    } else {
-        s0 = ((int64_t)blockIdx.x * nwaves + wave) * cs;
-        s_end = P.n;
-        s_step = (int64_t)gridDim.x * nwaves * cs;
-    }
-    // Each chunk reads the parameter block through a pointer that the compiler
+    // The loops read the parameter block through a pointer that the compiler
     // cannot see through, so that it loads a phase's fields where they are used:
-    // all of them loaded once before the loop do not fit the scalar registers,
+    // all of them loaded once before the loops do not fit the scalar registers,
     // and every use then reads a spill.
     using KernArg = const __attribute__((address_space(4))) LGParams<T>*;
-    for (; s0 < s_end; s0 += s_step) {
+    auto params = []() -> const LGParams<T>& {
         KernArg kp = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(kp));
-        const LGParams<T>& Q = *(const LGParams<T>*)kp;
-        lg_chunk<T, D, LANES, VEC, SCATTER>(Q, s0, Q.passes, lane, priv, bkey, by, block_s0, tiled, scale, lacc,
-                                            Q.sc.step);
+        return *(const LGParams<T>*)kp;
+    };
+    // tiled launches sort the samples [j*spb, (j+1)*spb) together, one such
+    // block after the other where there are more of them than workgroups (only
+    // with LDS-private modes); else the chunks go round the wavefronts
+    for (int64_t j = blockIdx.x;;) {
+        const LGParams<T>& B = params();
+        const int64_t b0 = tiled ? j * B.spb : 0;
+        const int64_t b1 = tiled ? std::min<int64_t>(B.n, b0 + B.spb) : B.n;
+        const int first = tiled ? wave : (int)blockIdx.x * nwaves + wave;
+        const int64_t s_step = (int64_t)(tiled ? nwaves : nwaves * (int)gridDim.x) * B.chunk_samples;
+        for (int64_t s0 = b0 + (int64_t)first * B.chunk_samples; s0 < b1; s0 += s_step) {
+            const LGParams<T>& Q = params();
+            lg_chunk<T, D, LANES, VEC, SCATTER>(Q, s0, Q.passes, lane, priv, bkey, by, b0, tiled, scale, lacc,
+                                                Q.sc.step);
+        }
+        const LGParams<T>& W = params();
+        if (tiled && !W.loss_only) bucket_write_out<T, D>(W, j, (int)(b1 - b0), bkey, by, bcnt, boff);
+        j += gridDim.x;
+        if (!SCATTER || !tiled || j >= W.nblocks) break;
     }
 
     if (P.loss_out) {
@@ -102,8 +106,6 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_
             }
         }
     }
-    if (tiled && !P.loss_only)
-        bucket_write_out<T, D>(P, blockIdx.x, (int)std::min<int64_t>(P.spb, P.n - block_s0), bkey, by, bcnt, boff);
 }
 
 // Row-block owner pass of the bucketed scatter.  Workgroup (b, split) owns

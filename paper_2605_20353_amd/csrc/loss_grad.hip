@@ -281,14 +281,20 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     int64_t grid;
     st = prepare_lds(reinterpret_cast<const void*>(kern), lds_bytes, t->device);
     if (st != GCP_OK) return st;
-    if (bucket_mask) {
-        grid = nblocks;
-    } else {
-        int per_cu = 0;
+    int per_cu = 0;
+    if (!bucket_mask || lds_mask) {
         GCP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), block,
                                                             lds_bytes));
         if (per_cu < 1) return set_error(GCP_ERR_UNSUPPORTED, "kernel does not fit on a CU (LDS %zu B)", lds_bytes);
-        const int64_t resident = (int64_t)per_cu * cus;
+    }
+    const int64_t resident = (int64_t)per_cu * cus;
+    if (bucket_mask) {
+        // with LDS-private modes no more workgroups than run at once: each adds
+        // its private gradient to G when it ends, one atomic request a 128-byte
+        // line at 10 G/s (5-way tensor of 1050 rank-20 rows: 782 workgroups'
+        // adds took 50 us of a 105 us launch)
+        grid = lds_mask ? std::min<int64_t>(nblocks, resident) : nblocks;
+    } else {
         grid = std::max<int64_t>(1, std::min<int64_t>(resident, ceil_div(nchunks, nwaves)));
         if (tile && tile->grid > 0) grid = tile->grid;
     }
