@@ -267,8 +267,7 @@ gcp_status launch_det(gcp_tensor_s* t, const gcp_sample_params* sp, const void* 
     if (n == 0) {
         if (!accumulate) {
             const int64_t gn = (int64_t)rows * R;
-            const unsigned zb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(gn, 256), 4096));
-            k_zero<T><<<zb, 256, 0, stream>>>((T*)G_out, gn, loss_out);
+            k_zero<T><<<zero_blocks(gn, (int)sizeof(T)), 256, 0, stream>>>((T*)G_out, gn, loss_out);
             GCP_HIP(hipGetLastError());
         }
         return GCP_OK;
@@ -302,8 +301,7 @@ gcp_status launch_det(gcp_tensor_s* t, const gcp_sample_params* sp, const void* 
     //    are, or 0 when the call does not accumulate)
     if (!accumulate) {
         const int64_t gn = (int64_t)rows * R;
-        const unsigned zb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(gn, 256), (int64_t)cus * 16));
-        k_zero<T><<<zb, 256, 0, stream>>>((T*)G_out, gn, nullptr);
+        k_zero<T><<<zero_blocks(gn, (int)sizeof(T)), 256, 0, stream>>>((T*)G_out, gn, nullptr);
         GCP_HIP(hipGetLastError());
     }
     const int64_t max_runs = std::min<int64_t>(rows, pairs);

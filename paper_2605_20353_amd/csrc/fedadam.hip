@@ -258,64 +258,95 @@ __global__ void __launch_bounds__(1024, (sizeof(T) == 4 && D > 0 ? 8 : 4)) k_fed
     for (int64_t e = threadIdx.x; e < rows * P.R; e += blockDim.x) dst[e] = part[e];
 }
 
+// V consecutive elements as one access (V = 1, or 16 bytes).
+template <typename T, int V>
+struct alignas(V * sizeof(T)) Pack {
+    T v[V];
+};
+
 // Adam on every client's model (blockIdx.y = client) for local step j,
-// re-zeroing G_c.
-template <typename T>
+// re-zeroing G_c (zeros are left as they are).
+template <typename T, int V>
 __global__ void __launch_bounds__(256) k_fed_adam(const FedArgs<T> F, int j)
 {
+    using P = Pack<T, V>;
     const FedClientDev<T>& C = F.clients[blockIdx.y];
-    T* M = const_cast<T*>(C.P.A);
-    T* G = C.P.G;
+    P* M = reinterpret_cast<P*>(const_cast<T*>(C.P.A));
+    P* G = reinterpret_cast<P*>(C.P.G);
+    P* B = reinterpret_cast<P*>(C.B);
+    P* Cm = reinterpret_cast<P*>(C.C);
     const int64_t t = *F.round * F.tau + j + 1;
     const T c1 = bias_correction<T>(F.b1d, t), c2 = bias_correction<T>(F.b2d, t);
-    const int64_t n = C.nparams;
+    const int64_t n = C.nparams / V;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        T p = M[e], b = C.B[e], cc = C.C[e];
-        adam_update<T>(p, G[e], b, cc, F.lr, F.b1, F.b2, F.one_m_b1, F.one_m_b2, c1, c2, F.eps, F.lower);
+        P p = M[e], b = B[e], c = Cm[e];
+        const P g = G[e];
+        bool zero = true;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            adam_update<T>(p.v[v], g.v[v], b.v[v], c.v[v], F.lr, F.b1, F.b2, F.one_m_b1, F.one_m_b2, c1, c2, F.eps,
+                           F.lower);
+            zero = zero && g.v[v] == T(0) && !__builtin_signbit(g.v[v]);
+        }
         M[e] = p;
-        C.B[e] = b;
-        C.C[e] = cc;
-        G[e] = T(0);
+        B[e] = b;
+        Cm[e] = c;
+        if (!zero) G[e] = P{};
     }
 }
 
 // Server step: D = per-row mean over covering clients of U - M_c, then Adam
 // on U with rate meta; also clears the clients' barrier counters.  Skipped
-// (counters still cleared) when a group barrier of the round gave up.
-template <typename T>
+// (counters still cleared) when a group barrier of the round gave up.  A
+// thread takes V columns of a row, so that the row's client list is walked
+// once for them.
+template <typename T, int V>
 __global__ void __launch_bounds__(256) k_fed_server(const FedArgs<T> F)
 {
+    using P = Pack<T, V>;
     const int64_t t = *F.round + 1;
     const T c1 = bias_correction<T>(F.b1d, t), c2 = bias_correction<T>(F.b2d, t);
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t nserver = barrier_failed(F.status) ? 0 : F.nserver;
-    for (int64_t e = gid; e < nserver; e += stride) {
-        const int64_t row = e / F.R, col = e - row * F.R;
+    const int64_t n = barrier_failed(F.status) ? 0 : F.nserver / V;
+    const uint32_t rv = (uint32_t)(F.R / V);
+    for (int64_t e = gid; e < n; e += stride) {
+        const int64_t row = n < (int64_t(1) << 32) ? (int64_t)((uint32_t)e / rv) : e / rv;
+        const int64_t col = e - row * rv;
         const int64_t b = F.cov_ptr[row], end = F.cov_ptr[row + 1];
-        T u = F.U[e];
-        T g = T(0);
-        for (int64_t i = b; i < end; ++i) g += u - F.Mptrs[F.cov_client[i]][(int64_t)F.cov_lrow[i] * F.R + col];
-        if (end > b) g /= T(end - b);
-        T bs = F.Bs[e], cs = F.Cs[e];
-        adam_update<T>(u, g, bs, cs, F.meta, F.b1, F.b2, F.one_m_b1, F.one_m_b2, c1, c2, F.eps, F.lower);
-        F.U[e] = u;
-        F.Bs[e] = bs;
-        F.Cs[e] = cs;
+        P u = reinterpret_cast<P*>(F.U)[e];
+        P g{};
+        for (int64_t i = b; i < end; ++i) {
+            const P m = reinterpret_cast<const P*>(F.Mptrs[F.cov_client[i]])[(int64_t)F.cov_lrow[i] * rv + col];
+#pragma unroll
+            for (int v = 0; v < V; ++v) g.v[v] += u.v[v] - m.v[v];
+        }
+        P bs = reinterpret_cast<P*>(F.Bs)[e], cs = reinterpret_cast<P*>(F.Cs)[e];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            if (end > b) g.v[v] /= T(end - b);
+            adam_update<T>(u.v[v], g.v[v], bs.v[v], cs.v[v], F.meta, F.b1, F.b2, F.one_m_b1, F.one_m_b2, c1, c2, F.eps,
+                           F.lower);
+        }
+        reinterpret_cast<P*>(F.U)[e] = u;
+        reinterpret_cast<P*>(F.Bs)[e] = bs;
+        reinterpret_cast<P*>(F.Cs)[e] = cs;
     }
     if (gid < F.K) F.barrier[gid] = 0;
 }
 
-// Per-client launches: M_c <- rows of U (blockIdx.y = client).
-template <typename T>
+// M_c <- rows of U (blockIdx.y = client).
+template <typename T, int V>
 __global__ void __launch_bounds__(256) k_fed_copy(const FedArgs<T> F)
 {
+    using P = Pack<T, V>;
     const FedClientDev<T>& C = F.clients[blockIdx.y];
-    T* M = const_cast<T*>(C.P.A);
+    P* M = reinterpret_cast<P*>(const_cast<T*>(C.P.A));
+    const P* U = reinterpret_cast<const P*>(F.U);
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t n = (int64_t)gridDim.x * blockDim.x;
     for (int k = 0; k < F.d; ++k)
-        for (int64_t e = tid; e < C.seg_len[k]; e += n) M[C.seg_dst[k] + e] = F.U[C.seg_src[k] + e];
+        for (int64_t e = tid; e < C.seg_len[k] / V; e += n) M[C.seg_dst[k] / V + e] = U[C.seg_src[k] / V + e];
 }
 
 __global__ void k_fed_set_round(int64_t* round, int64_t value) { *round = value; }
@@ -409,6 +440,7 @@ struct gcp_fed_s {
     int owner_block = 1024;        // threads of an owner workgroup
     int nb_max = 0;                // row blocks of the largest client
     int64_t max_params = 0;        // parameters of the largest client
+    int pack = 1;                  // elements per access of the streaming kernels
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t graph_stream = nullptr;
@@ -448,6 +480,14 @@ static gcp_status fed_build(gcp_fed_s* f)
                 cov_l[fill[g]] = (int)(t->rowoff[k] + r);
                 ++fill[g];
             }
+    }
+    // 16-byte accesses where rows and buffers are made of whole ones
+    {
+        uintptr_t at = (uintptr_t)D.U | (uintptr_t)D.Bs | (uintptr_t)D.Cs;
+        for (const gcp_fed_client& cl : f->clients)
+            at |= (uintptr_t)cl.M | (uintptr_t)cl.B | (uintptr_t)cl.C | (uintptr_t)cl.G;
+        const int pack = 16 / (int)sizeof(T);
+        f->pack = at % 16 == 0 && R % pack == 0 ? pack : 1;
     }
     // small modes of the batched kernel accumulate in LDS (per workgroup and
     // local step) when the largest client block of the mode fits the budget
@@ -695,6 +735,31 @@ static gcp_status fed_build(gcp_fed_s* f)
     return GCP_OK;
 }
 
+// Workgroups that give each thread one access of `pack` elements.
+static unsigned fed_blocks(int64_t elems, int pack)
+{
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(elems, (int64_t)256 * pack), int64_t(1) << 20));
+}
+
+template <typename T>
+static void fed_copy(gcp_fed_s* f, int64_t maxlen, hipStream_t stream)
+{
+    const FedArgs<T>& a = *reinterpret_cast<const FedArgs<T>*>(f->args);
+    const dim3 grid(fed_blocks(maxlen, f->pack), (unsigned)f->desc.nclients);
+    if (f->pack > 1) k_fed_copy<T, 16 / sizeof(T)><<<grid, 256, 0, stream>>>(a);
+    else k_fed_copy<T, 1><<<grid, 256, 0, stream>>>(a);
+}
+
+template <typename T>
+static void fed_server(gcp_fed_s* f, hipStream_t stream)
+{
+    const FedArgs<T>& a = *reinterpret_cast<const FedArgs<T>*>(f->args);
+    // at least one thread per client (the barrier counters)
+    const unsigned grid = std::max(fed_blocks(f->nserver, f->pack), fed_blocks(f->desc.nclients, 1));
+    if (f->pack > 1) k_fed_server<T, 16 / sizeof(T)><<<grid, 256, 0, stream>>>(a);
+    else k_fed_server<T, 1><<<grid, 256, 0, stream>>>(a);
+}
+
 template <typename T>
 static gcp_status fed_launch_batched(gcp_fed_s* f, hipStream_t stream)
 {
@@ -703,10 +768,9 @@ static gcp_status fed_launch_batched(gcp_fed_s* f, hipStream_t stream)
     if (f->bucketed) {
         int64_t maxlen = 0;
         for (const gcp_fed_client& cl : f->clients) maxlen = std::max<int64_t>(maxlen, cl.tensor->rowoff[f->d] * f->desc.R);
-        const unsigned cb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(maxlen, 256), 1024));
-        k_fed_copy<T><<<dim3(cb, K), 256, 0, stream>>>(a);
+        fed_copy<T>(f, maxlen, stream);
         GCP_HIP(hipGetLastError());
-        const unsigned ab = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(f->max_params, 256 * 4), 256));
+        const unsigned ab = fed_blocks(f->max_params, f->pack);
         for (int j = 0; j < f->desc.tau; ++j) {
             hipLaunchKernelGGL(reinterpret_cast<FedStepKernel<T>>(const_cast<void*>(f->sample_kernel)),
                                dim3((unsigned)f->W, K), dim3(f->block), f->sample_lds, stream, a, j);
@@ -714,7 +778,8 @@ static gcp_status fed_launch_batched(gcp_fed_s* f, hipStream_t stream)
             hipLaunchKernelGGL(reinterpret_cast<FedKernel<T>>(const_cast<void*>(f->owner_kernel)),
                                dim3((unsigned)f->nb_max, K), dim3(f->owner_block), f->owner_lds, stream, a);
             GCP_HIP(hipGetLastError());
-            k_fed_adam<T><<<dim3(ab, K), 256, 0, stream>>>(a, j);
+            if (f->pack > 1) k_fed_adam<T, 16 / sizeof(T)><<<dim3(ab, K), 256, 0, stream>>>(a, j);
+            else k_fed_adam<T, 1><<<dim3(ab, K), 256, 0, stream>>>(a, j);
             GCP_HIP(hipGetLastError());
         }
     } else {
@@ -722,8 +787,7 @@ static gcp_status fed_launch_batched(gcp_fed_s* f, hipStream_t stream)
                            dim3(K * (unsigned)f->W), dim3(f->block), f->client_lds, stream, a);
         GCP_HIP(hipGetLastError());
     }
-    const int64_t sb = std::max<int64_t>(1, std::min<int64_t>(ceil_div(f->nserver, 256), 2048));
-    k_fed_server<T><<<(unsigned)sb, 256, 0, stream>>>(a);
+    fed_server<T>(f, stream);
     GCP_HIP(hipGetLastError());
     return GCP_OK;
 }
@@ -731,12 +795,10 @@ static gcp_status fed_launch_batched(gcp_fed_s* f, hipStream_t stream)
 template <typename T>
 static gcp_status fed_round_plain(gcp_fed_s* f, int64_t round, hipStream_t stream)
 {
-    const FedArgs<T>& a = *reinterpret_cast<const FedArgs<T>*>(f->args);
     const gcp_fed_desc& D = f->desc;
     int64_t maxlen = 0;
     for (const gcp_fed_client& cl : f->clients) maxlen = std::max<int64_t>(maxlen, cl.tensor->rowoff[f->d] * D.R);
-    const unsigned cb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(maxlen, 256), 1024));
-    k_fed_copy<T><<<dim3(cb, (unsigned)D.nclients), 256, 0, stream>>>(a);
+    fed_copy<T>(f, maxlen, stream);
     GCP_HIP(hipGetLastError());
     gcp_tile tile{};
     // with the automatic scatter, each call also picks its own lane shape
@@ -765,8 +827,7 @@ static gcp_status fed_round_plain(gcp_fed_s* f, int64_t round, hipStream_t strea
             if (st != GCP_OK) return st;
         }
     }
-    const int64_t sb = std::max<int64_t>(1, std::min<int64_t>(ceil_div(f->nserver, 256), 2048));
-    k_fed_server<T><<<(unsigned)sb, 256, 0, stream>>>(a);
+    fed_server<T>(f, stream);
     GCP_HIP(hipGetLastError());
     return GCP_OK;
 }

@@ -144,12 +144,24 @@ __global__ void __launch_bounds__(1024, (sizeof(T) == 4 && D > 0 ? 8 : 4)) k_buc
     }
 }
 
+// Zeroes p[0, n) in 16-byte stores (single ones where p is not aligned) and the
+// objective.
 template <typename T>
-__global__ void k_zero(T* __restrict__ p, int64_t n, double* __restrict__ loss_out)
+__global__ void __launch_bounds__(256) k_zero(T* __restrict__ p, int64_t n, double* __restrict__ loss_out)
 {
+    constexpr int V = 16 / sizeof(T);
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     if (i0 == 0 && loss_out) *loss_out = 0.0;
-    for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = T(0);
+    const int64_t nv = (uintptr_t)p % 16 == 0 ? n / V : 0;
+    for (int64_t i = i0; i < nv; i += stride) reinterpret_cast<uint4*>(p)[i] = uint4{0, 0, 0, 0};
+    for (int64_t i = nv * V + i0; i < n; i += stride) p[i] = T(0);
+}
+
+// Workgroups of a k_zero launch over n elements of `bytes` bytes.
+inline unsigned zero_blocks(int64_t n, int bytes)
+{
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n * bytes, 16 * 256), int64_t(1) << 30));
 }
 
 template <typename T>

@@ -348,8 +348,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     if (!accumulate) {
         const int64_t gn = loss_only ? 0 : t->rowoff[d] * R;
         if (gn > 0 || loss_out) {
-            int64_t zb = std::max<int64_t>(1, std::min<int64_t>(ceil_div(gn, 256), 4096));
-            k_zero<T><<<(unsigned)zb, 256, 0, stream>>>((T*)G_out, gn, loss_out);
+            k_zero<T><<<zero_blocks(gn, (int)sizeof(T)), 256, 0, stream>>>((T*)G_out, gn, loss_out);
             GCP_HIP(hipGetLastError());
         }
     }
