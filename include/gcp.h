@@ -140,7 +140,7 @@ typedef struct gcp_tile {
                                      ceil(J / bucket_splits) of the J sort
                                      segments); 0 = auto                    */
     int32_t bucket_block;         /* threads per row-block workgroup, multiple
-                                     of 64 up to 1024; 0 = 1024             */
+                                     of 64 up to 1024; 0 = auto              */
 } gcp_tile;
 
 /* gcp_loss_grad flags */

@@ -107,7 +107,18 @@ constexpr int kMaxBuckets = 4096;
 // gather, evaluate and atomic adds one after the other (35 us); 8-sample
 // chunks take 22 us.
 constexpr int kWavesPerCu = 16;
-constexpr int kBucketWgPerCu = 8;              // owner-pass workgroups per CU aimed at
+// Owner-pass workgroups: one per kOwnerEntries entries, within 2 to 8 per CU.
+// Every workgroup flushes its row block, one atomic request a 128-byte line at
+// 10 G/s, while about 50 G entries/s go through at rank 32: with 8 per CU at
+// every size, 2^20 samples of a 25000-row mode spent 40 of 49 us on flushes
+// (call 131 us, 110 us with 512 workgroups); 2^21 samples of 24000 rows are
+// indifferent from 768 to 2112 workgroups.
+constexpr int kOwnerEntries = 4096;
+constexpr int kOwnerWgPerCuMin = 2, kOwnerWgPerCuMax = 8;
+// Threads of an owner workgroup: 512 from this many entries on (2^21 samples of
+// three modes: 210 us a call, 220 us with 1024), below it 1024, whose fewer
+// workgroups flush less (2^17 samples: 29 us, 33 us with 512).
+constexpr int64_t kOwnerSmallBlockEntries = 1 << 20;
 
 template <typename T>
 static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_params* sp, const gcp_samples* smp,
@@ -358,20 +369,21 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     if (bucket_mask) {
         BAKernel<T> bk = pick_bucket_kernel<T>(order, lanes, vec);
         if (!bk) return set_error(GCP_ERR_UNSUPPORTED, "no bucket kernel for lanes = %d, vec = %d", lanes, vec);
-        const int bblock = (tile && tile->bucket_block > 0) ? tile->bucket_block : 1024;
+        const int bblock = (tile && tile->bucket_block > 0)              ? tile->bucket_block
+                           : n * (int64_t)nbm >= kOwnerSmallBlockEntries ? 512
+                                                                         : 1024;
         if (bblock % 64 != 0 || bblock > 1024) return set_error(GCP_ERR_ARG, "bucket_block = %d", bblock);
         const int bwaves = bblock / 64;
         // workgroups per row block: proportional to the entries a row block
         // of the mode expects (n * rows per block / I_k, samples uniform over
-        // the rows), aiming at kBucketWgPerCu owner workgroups per CU.  Each
-        // workgroup reads a whole number of segments per wave, since its waves
-        // take its segments in turn and one wave with an extra segment would
-        // hold up the workgroup
+        // the rows).  Each workgroup reads a whole number of segments per wave,
+        // since its waves take its segments in turn and one wave with an extra
+        // segment would hold up the workgroup
         const int64_t rows_blk = int64_t(1) << br_shift;
-        double expect_total = 0.0;
-        for (int k = 0; k < d; ++k)
-            if ((bucket_mask >> k) & 1u) expect_total += (double)n;
-        const double per_wg = std::max(1.0, expect_total / ((double)kBucketWgPerCu * cus));
+        const double entries = (double)n * nbm;
+        const double per_wg =
+            std::max(1.0, entries / std::max<double>((double)kOwnerWgPerCuMin * cus,
+                                                     std::min<double>((double)kOwnerWgPerCuMax * cus, entries / kOwnerEntries)));
         int64_t wg = 0;
         for (int k = 0; k < d; ++k) {
             P.bwg_base[k] = wg;
