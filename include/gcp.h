@@ -212,7 +212,7 @@ int64_t gcp_tensor_device_bytes(gcp_tensor t);
  * (sort-by-row MTTKRP, Sec. 3.1.2) and for GCP_DETERMINISTIC calls, for calls
  * with up to max_samples = p + q samples at rank R: about 16 (max_samples +
  * 8192) d bytes of sample entries plus per-(row block, workgroup) counts, or
- * what the deterministic form needs (coordinates and derivative values of
+ * what the deterministic form needs (cell keys and derivative values of
  * the sampled tensor, (row, sample) pairs and their sort), whichever is
  * larger.  Without a reservation every large
  * mode uses hardware atomics.  Calls that use the workspace of one handle

@@ -4,14 +4,15 @@
 // order that depends on timing (atomics, LDS compare-and-swap, per-workgroup
 // flushes); here every sum has a fixed order:
 //   1. the sampling kernel (k_loss_grad, src = 2) writes the sampled tensor
-//      -- coordinates and y = w f'(x, m) of every sample -- and each
+//      -- the cell's key and y = w f'(x, m) of every sample -- and each
 //      wavefront's partial objective into its own slot;
 //   2. k_det_pairs lists (model row, sample) for every sample and mode;
 //   3. a stable radix sort by row (rocPRIM) groups each row's samples in
 //      sample order;
-//   4. k_det_starts finds where each row's run begins, and rocPRIM's unique
-//      lists the rows whose run is not empty (in row order);
-//   5. k_det_reduce gives each listed gradient row to one lane group, which adds
+//   4. k_det_starts finds where each row's run begins, and, where there are
+//      more rows than pairs, rocPRIM's unique lists the rows whose run is not
+//      empty (in row order);
+//   5. k_det_reduce gives each gradient row to one lane group, which adds
 //      y prod_{j != k} A_j[i_j, :] over the row's run in an order fixed by
 //      the sorted run (the sampled MTTKRP of eq. gcp-gradient, Sec. 3.1.2)
 //      and writes the row;
@@ -30,15 +31,20 @@ struct DetModes {
 };
 
 // (row, sample) of mode k for sample s at k * n + s.
-__global__ void __launch_bounds__(256) k_det_pairs(const int64_t* __restrict__ coords, int64_t n, DetModes M,
+__global__ void __launch_bounds__(256) k_det_pairs(const uint4* __restrict__ rec, int64_t n, DetModes M, KeyLayout L,
                                                    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals)
 {
-    const int64_t total = n * M.d;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t k = i / n, s = i - k * n;
-        keys[i] = M.rowoff[k] + (uint32_t)coords[s * M.d + k];
-        vals[i] = (uint32_t)s;
+    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n; s += (int64_t)gridDim.x * blockDim.x) {
+        const uint2 w = *reinterpret_cast<const uint2*>(rec + s);
+        uint32_t ci[kMaxModes];
+        unpack_all<true>(L, M.d, (uint64_t)w.x | ((uint64_t)w.y << 32), ci);
+#pragma unroll
+        for (int k = 0; k < kMaxModes; ++k) {
+            if (k < M.d) {
+                keys[k * n + s] = M.rowoff[k] + ci[k];
+                vals[k * n + s] = (uint32_t)s;
+            }
+        }
     }
 }
 
@@ -55,12 +61,12 @@ __global__ void __launch_bounds__(256) k_det_starts(const uint32_t* __restrict__
     }
 }
 
-// Lanes per gradient row in k_det_reduce: R rounded up to a power of two,
-// at most 64.
-__host__ __device__ inline int det_group_lanes(int R)
+// Lanes per gradient row in k_det_reduce at VEC columns per lane: enough for R
+// columns, a power of two, at most 64.
+__host__ __device__ inline int det_group_lanes(int R, int vec)
 {
     int rp = 1;
-    while (rp < R && rp < 64) rp <<= 1;
+    while (rp * vec < R && rp < 64) rp <<= 1;
     return rp;
 }
 
@@ -75,83 +81,120 @@ __device__ __forceinline__ double lane_get(double v, int src)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// One lane group per gradient row: RP lanes (RP = R rounded up to a power of
-// two, at most 64; wider ranks take the columns 64 at a time), so a
-// wavefront holds H = 64 / RP rows at once.  A group reads its row's run of
-// sorted (row, sample) pairs RP at a time, one pair per lane: the lane loads
-// the sample's y and the model rows of the other modes.  Lane shuffles inside
-// the group then hand the pairs out in run order; the group gathers the other
-// modes' rows and adds y prod_{j != k} A_j[i_j, :] in that order.  Every sum
-// thus has an order fixed by the sorted run alone.  Only the listed rows
-// (those with pairs) are visited; when the call does not accumulate, G is zeroed
-// before this kernel, so rows without pairs hold 0.
-template <typename T, int D>
+// One lane group per gradient row: RP lanes of VEC columns (wider ranks take
+// the columns RP VEC at a time), so a wavefront holds H = 64 / RP rows at once.
+// A group reads its row's run of sorted (row, sample) pairs RP at a time, one
+// pair per lane: the lane loads the sample's y and the model rows of the other
+// modes.  Lane shuffles inside the group then hand the pairs out in run order;
+// the group gathers the other modes' rows and adds y prod_{j != k} A_j[i_j, :]
+// in that order.  Every sum thus has an order fixed by the sorted run alone.
+// Bound by the records' random 16 bytes, a whole line out of the Infinity
+// Cache each.  A batch's samples are read two batches ahead, its records one
+// ahead, and U pairs' rows are in flight at once.  16 bytes per lane: a load instruction costs the
+// vector memory path the same whatever its width (2^20 samples, rank 32: 142 us
+// with one column per lane and no read-ahead).
+// runs: the rows to visit (those with pairs); NULL visits every row, and rows
+// without pairs get 0 when the call does not accumulate.
+template <typename T, int D, int VEC>
 __global__ void __launch_bounds__(256) k_det_reduce(const uint32_t* __restrict__ start,
                                                     const uint32_t* __restrict__ runs,
-                                                    const uint32_t* __restrict__ nruns,
+                                                    const uint32_t* __restrict__ nruns, uint32_t rows,
                                                     const uint32_t* __restrict__ svals,
-                                                    const int64_t* __restrict__ coords, const T* __restrict__ y,
-                                                    const T* __restrict__ A, DetModes M, int R,
+                                                    const uint4* __restrict__ rec, const T* __restrict__ A, DetModes M,
+                                                    KeyLayout L, int R,
                                                     const T* __restrict__ scale, int accumulate, T* __restrict__ G)
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
     constexpr int DO = DM - 1;
-    constexpr int U = 4;
+    constexpr int U = D > 0 && DO * VEC * (int)sizeof(T) <= 48 ? 8 : 4;
     const int dd = D > 0 ? D : M.d;
     const int lane = threadIdx.x & 63;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const T sc = scale ? *scale : T(1);
-    const int RP = det_group_lanes(R);
+    const int RP = det_group_lanes(R, VEC);
     const int H = 64 / RP;
     const int h = lane / RP, cg = lane % RP, gl0 = h * RP;
-    const int64_t nr = *nruns;
+    const int64_t nr = runs ? (int64_t)*nruns : (int64_t)rows;
     for (int64_t j0 = wave * H; j0 < nr; j0 += nw * H) {
         const int64_t j = j0 + h;
         if (j >= nr) break;               // no row for this group; shuffles stay inside a group
-        const uint32_t r = runs[j];
+        const uint32_t r = runs ? runs[j] : (uint32_t)j;
         int k = 0;
         for (int kk = 1; kk < dd; ++kk)
             if (M.rowoff[kk] <= r) k = kk;
         const uint32_t b = start[r], e = start[r + 1];
-        for (int c0 = 0; c0 < R; c0 += RP) {
-            const int c = c0 + cg;
+        if (b == e && accumulate) continue;
+        for (int c0 = 0; c0 < R; c0 += RP * VEC) {
+            const int c = c0 + cg * VEC;
             const bool col = c < R;
             const uint64_t colL = col ? (uint32_t)c : 0u;
-            T acc = T(0);
+            T acc[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[v] = T(0);
+            // lane cg of the group: pair i0 + cg (past the run's end: its last pair)
+            auto sample = [&](uint32_t i0) { return svals[min(i0 + (uint32_t)cg, e - 1)]; };
+            T yl = T(0);
+            uint32_t orow[DO], s1 = 0;
+            auto pair = [&](uint32_t sl) {
+                const uint4 w = rec[sl];
+                yl = entry_y<T>(w) * sc;
+                uint32_t ci[DM];
+                unpack_all<true>(L, dd, (uint64_t)w.x | ((uint64_t)w.y << 32), ci);
+                // slot o holds mode o, or o + 1 from k on
+#pragma unroll
+                for (int o = 0; o < DO; ++o)
+                    orow[o] = o >= k ? M.rowoff[o + 1] + ci[o + 1] : M.rowoff[o] + ci[o];
+            };
+            if (b < e) {
+                pair(sample(b));
+                s1 = sample(b + (uint32_t)RP);
+            }
             for (uint32_t i0 = b; i0 < e; i0 += (uint32_t)RP) {
                 const uint32_t nv = min(e - i0, (uint32_t)RP);
-                // lane cg of the group: pair i0 + cg (past the run's end: its last pair)
-                const uint32_t sl = svals[i0 + min((uint32_t)cg, nv - 1)];
-                const T yl = y[sl] * sc;
-                uint32_t orow[DO];
+                const T yc = yl;
+                uint32_t oc[DO];
 #pragma unroll
-                for (int o = 0; o < DO; ++o) {
-                    const int m = o + (o >= k ? 1 : 0);
-                    orow[o] = (D > 0 || m < dd) ? M.rowoff[m] + (uint32_t)coords[(uint64_t)sl * dd + m] : 0u;
-                }
+                for (int o = 0; o < DO; ++o) oc[o] = orow[o];
                 for (uint32_t q0 = 0; q0 < nv; q0 += U) {
-                    T yq[U], prod[U];
+                    T yq[U], a[U][DO][VEC];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int q = gl0 + (int)min(q0 + (uint32_t)u, nv - 1);
-                        yq[u] = lane_get(yl, q);
-                        prod[u] = T(1);
+                        yq[u] = lane_get(yc, q);
 #pragma unroll
                         for (int o = 0; o < DO; ++o) {
                             if (D == 0 && o >= dd - 1) break;
-                            const uint32_t row = (uint32_t)__shfl((int)orow[o], q, 64);
-                            prod[u] *= A[(uint64_t)row * (uint32_t)R + colL];
+                            const uint32_t row = (uint32_t)__shfl((int)oc[o], q, 64);
+                            load_cols<T, VEC>(A + (uint64_t)row * (uint32_t)R + colL, a[u][o]);
                         }
                     }
+                    // the next batch's loads go out behind this one's gathers:
+                    // loads return in order
+                    __asm__ volatile("" ::: "memory");
+                    if (q0 == 0) {
+                        const uint32_t s2 = s1;
+                        s1 = sample(i0 + 2u * (uint32_t)RP);
+                        pair(s2);
+                    }
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        if (q0 + (uint32_t)u < nv) acc += yq[u] * prod[u];
+                    for (int u = 0; u < U; ++u) {
+                        if (q0 + (uint32_t)u >= nv) continue;
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) {
+                            T prod = T(1);
+#pragma unroll
+                            for (int o = 0; o < DO; ++o)
+                                if (D > 0 || o < dd - 1) prod *= a[u][o][v];
+                            acc[v] += yq[u] * prod;
+                        }
+                    }
                 }
             }
             if (col) {
                 T* g = G + (uint64_t)r * (uint32_t)R + c;
-                *g = accumulate ? *g + acc : acc;
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) g[v] = accumulate ? g[v] + acc[v] : acc[v];
             }
         }
     }
@@ -185,7 +228,7 @@ int sort_bits(uint32_t rows)
 }
 
 struct DetLayout {
-    int64_t coords, y, keys_in, vals_in, keys_out, vals_out, start, runs, nruns, parts, scratch_loss, sort_tmp, total;
+    int64_t rec, keys_in, vals_in, keys_out, vals_out, start, runs, nruns, parts, scratch_loss, sort_tmp, total;
     size_t sort_bytes;
 };
 
@@ -193,7 +236,6 @@ int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
 
 gcp_status det_layout(const gcp_tensor_s* t, int64_t n, DetLayout& L)
 {
-    const int64_t esize = t->dt == GCP_F32 ? 4 : 8;
     const int64_t pairs = n * t->d;
     const uint32_t rows = (uint32_t)t->rowoff[t->d];
     L.sort_bytes = 0;
@@ -207,8 +249,7 @@ gcp_status det_layout(const gcp_tensor_s* t, int64_t n, DetLayout& L)
     if (e != hipSuccess) return hip_error(e, "rocprim::unique (size query)");
     L.sort_bytes = std::max(L.sort_bytes, unique_bytes);          // the two use the region one after the other
     int64_t off = 0;
-    L.coords = off; off = align256(off + pairs * 8);
-    L.y = off; off = align256(off + n * esize);
+    L.rec = off; off = align256(off + n * 16);
     L.keys_in = off; off = align256(off + pairs * 4);
     L.vals_in = off; off = align256(off + pairs * 4);
     L.keys_out = off; off = align256(off + pairs * 4);
@@ -251,8 +292,7 @@ gcp_status launch_det(gcp_tensor_s* t, const gcp_sample_params* sp, const void* 
     //    launch's own objective target is a scratch word, so that loss_out
     //    keeps its accumulate semantics
     LGOutputs xo;
-    xo.y_out = ws + L.y;
-    xo.coords_out = (int64_t*)(ws + L.coords);
+    xo.rec_out = ws + L.rec;
     xo.loss_parts = loss_out ? (double*)(ws + L.parts) : nullptr;
     xo.loss_parts_cap = kDetLossSlots;
     int64_t parts = 0;
@@ -278,8 +318,8 @@ gcp_status launch_det(gcp_tensor_s* t, const gcp_sample_params* sp, const void* 
     const int cus = device_cu_count(t->device);
     const int64_t pairs = n * t->d;
     // 2. (row, sample) pairs
-    const unsigned pg = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(pairs, 256), (int64_t)cus * 16));
-    hipLaunchKernelGGL(k_det_pairs, dim3(pg), dim3(256), 0, stream, (const int64_t*)(ws + L.coords), n, M,
+    const unsigned pg = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256), (int64_t)cus * 64));
+    hipLaunchKernelGGL(k_det_pairs, dim3(pg), dim3(256), 0, stream, (const uint4*)(ws + L.rec), n, M, t->layout,
                        (uint32_t*)(ws + L.keys_in), (uint32_t*)(ws + L.vals_in));
     GCP_HIP(hipGetLastError());
     // 3. stable sort by row
@@ -293,26 +333,37 @@ gcp_status launch_det(gcp_tensor_s* t, const gcp_sample_params* sp, const void* 
     hipLaunchKernelGGL(k_det_starts, dim3(sg), dim3(256), 0, stream, (const uint32_t*)(ws + L.keys_out), pairs, rows,
                        (uint32_t*)(ws + L.start));
     GCP_HIP(hipGetLastError());
-    size_t unique_bytes = L.sort_bytes;
-    GCP_HIP(rocprim::unique(ws + L.sort_tmp, unique_bytes, (const uint32_t*)(ws + L.keys_out),
-                            (uint32_t*)(ws + L.runs), (uint32_t*)(ws + L.nruns), (size_t)pairs,
-                            rocprim::equal_to<uint32_t>(), stream));
-    // 5. one lane group per listed gradient row (all others stay as they
-    //    are, or 0 when the call does not accumulate)
-    if (!accumulate) {
-        const int64_t gn = (int64_t)rows * R;
-        k_zero<T><<<zero_blocks(gn, (int)sizeof(T)), 256, 0, stream>>>((T*)G_out, gn, nullptr);
-        GCP_HIP(hipGetLastError());
+    // 5. one lane group per gradient row: every row where there are no more
+    //    rows than pairs (24000 rows, 3.1M pairs: the list alone took 35 us),
+    //    else the list of those with pairs, the others staying as they are, or
+    //    0 when the call does not accumulate
+    const bool listed = (int64_t)rows > pairs;
+    if (listed) {
+        size_t unique_bytes = L.sort_bytes;
+        GCP_HIP(rocprim::unique(ws + L.sort_tmp, unique_bytes, (const uint32_t*)(ws + L.keys_out),
+                                (uint32_t*)(ws + L.runs), (uint32_t*)(ws + L.nruns), (size_t)pairs,
+                                rocprim::equal_to<uint32_t>(), stream));
+        if (!accumulate) {
+            const int64_t gn = (int64_t)rows * R;
+            k_zero<T><<<zero_blocks(gn, (int)sizeof(T)), 256, 0, stream>>>((T*)G_out, gn, nullptr);
+            GCP_HIP(hipGetLastError());
+        }
     }
     const int64_t max_runs = std::min<int64_t>(rows, pairs);
-    const int64_t rows_per_wg = 4 * (64 / det_group_lanes(R));          // 4 wavefronts of 64 / RP rows
+    constexpr int VW = 16 / (int)sizeof(T);
+    const bool wide = R % VW == 0 && (uintptr_t)A % 16 == 0;
+    const int64_t rows_per_wg = 4 * (64 / det_group_lanes(R, wide ? VW : 1));     // 4 wavefronts of 64 / RP rows
     const unsigned rg =
         (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(max_runs, rows_per_wg), (int64_t)cus * 32));
-    auto reduce = t->d == 3 ? k_det_reduce<T, 3> : t->d == 4 ? k_det_reduce<T, 4> : k_det_reduce<T, 0>;
+    auto reduce = wide ? (t->d == 3   ? k_det_reduce<T, 3, VW>
+                          : t->d == 4 ? k_det_reduce<T, 4, VW>
+                                      : k_det_reduce<T, 0, VW>)
+                       : (t->d == 3   ? k_det_reduce<T, 3, 1>
+                          : t->d == 4 ? k_det_reduce<T, 4, 1>
+                                      : k_det_reduce<T, 0, 1>);
     hipLaunchKernelGGL(reduce, dim3(rg), dim3(256), 0, stream, (const uint32_t*)(ws + L.start),
-                       (const uint32_t*)(ws + L.runs), (const uint32_t*)(ws + L.nruns),
-                       (const uint32_t*)(ws + L.vals_out), (const int64_t*)(ws + L.coords), (const T*)(ws + L.y),
-                       (const T*)A, M, R, (flags & GCP_SCALE_BY_DEV) ? (const T*)scale_dev : nullptr,
+                       listed ? (const uint32_t*)(ws + L.runs) : nullptr, (const uint32_t*)(ws + L.nruns), rows,
+                       (const uint32_t*)(ws + L.vals_out), (const uint4*)(ws + L.rec), (const T*)A, M, t->layout, R, (flags & GCP_SCALE_BY_DEV) ? (const T*)scale_dev : nullptr,
                        accumulate ? 1 : 0, (T*)G_out);
     GCP_HIP(hipGetLastError());
     // 6. the objective, partials in slot order

@@ -349,6 +349,7 @@ struct LGWorkspace {
 struct LGOutputs {
     void* y_out = nullptr;          // [n] tensor dtype
     int64_t* coords_out = nullptr;  // [n x d]
+    void* rec_out = nullptr;        // or, instead of the two: [n] 16-byte {cell key, y}
     double* loss_parts = nullptr;   // per-wave objective partials (deterministic objective)
     int64_t loss_parts_cap = 0;     // slots available
     int64_t* parts_used = nullptr;  // receives the number of slots the launch fills

@@ -58,6 +58,8 @@ struct LGParams {
     // offsets)
     T* y_out;
     int64_t* c_out;
+    // or, for the deterministic form, both in one 16-byte {key, y} a sample
+    uint4* rec_out;
     // deterministic objective: each wave's partial sum goes to its own slot
     // (workgroup * waves + wave) instead of an atomic add into loss_out
     double* loss_parts;
@@ -416,7 +418,7 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
                 for (int k = 0; k < DM; ++k)
                     if (k < dd) key += pack_coord(P.sc.L, (uint64_t)ci[k], k);
             }
-            if (P.src == 2) {
+            if (P.src == 2 && P.c_out) {
 #pragma unroll
                 for (int k = 0; k < DM; ++k)
                     if (k < dd) P.c_out[s * dd + k] = (int64_t)ci[k];
@@ -553,7 +555,10 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
             T l = T(0);
             const T y = given ? w * x : sample_y<T>(P, x, w, mown, s < P.sc.p, l);
             lacc += (double)l;
-            if (P.src == 2) P.y_out[s] = y;
+            if (P.src == 2) {
+                if (P.rec_out) P.rec_out[s] = pack_entry<T>(key, y);
+                else P.y_out[s] = y;
+            }
             if (tiled) by[s - block_s0] = y * scale;
         }
     }

@@ -130,7 +130,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     int64_t n = 0;
     gcp_status st = make_sample_ctx<T>(t, sp, P.sc, n);
     if (st != GCP_OK) return st;
-    const bool write_y = xo && xo->y_out;
+    const bool write_y = xo && (xo->y_out || xo->rec_out);
     const bool loss_only = (flags & GCP_LOSS_ONLY) != 0 || write_y;
     const bool given_values = (int)loss == kLossGivenValues;
     const bool accumulate = (flags & GCP_ACCUMULATE) != 0;
@@ -143,7 +143,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     if (!loss_only && !G_out) return set_error(GCP_ERR_ARG, "G_out is NULL");
     if ((flags & GCP_SCALE_BY_DEV) && !scale_dev) return set_error(GCP_ERR_ARG, "scale_dev is NULL");
     if (loss_only && !loss_out && !write_y) return set_error(GCP_ERR_ARG, "GCP_LOSS_ONLY without loss_out");
-    if (write_y && (smp || !xo->coords_out)) return set_error(GCP_ERR_ARG, "sampled-tensor output needs coords_out");
+    if (write_y && (smp || !(xo->coords_out || xo->rec_out))) return set_error(GCP_ERR_ARG, "sampled-tensor output needs coords_out");
     if (smp && (!smp->coords || !smp->x || (!smp->w && !given_values)) && n > 0)
         return set_error(GCP_ERR_ARG, "materialised sample list has a NULL array");
     if (given_values && loss_out) return set_error(GCP_ERR_ARG, "the MTTKRP of a given sampled tensor has no objective");
@@ -328,6 +328,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     if (write_y) {
         P.y_out = (T*)xo->y_out;
         P.c_out = xo->coords_out;
+        P.rec_out = (uint4*)xo->rec_out;
     }
     if (xo && xo->loss_parts && loss_out) {
         if (bucket_mask) return set_error(GCP_ERR_ARG, "per-wave objective partials need an unbucketed launch");
