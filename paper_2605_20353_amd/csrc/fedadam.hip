@@ -146,8 +146,8 @@ __global__ void __launch_bounds__(1024) k_fed_clients(const FedArgs<T> F)
             __syncthreads();
         }
         for (int64_t chunk = (int64_t)w * nwaves + wave; chunk < P.nchunks; chunk += (int64_t)F.W * nwaves)
-            lg_chunk<T, D, LANES, VEC, true>(P, chunk * 64, LANES, lane, priv, nullptr, nullptr, 0, false, T(1), lacc,
-                                             step);
+            lg_chunk<T, D, LANES, VEC, true>(P, chunk * 64, LANES, lane, priv, nullptr, nullptr, nullptr, 0, false,
+                                             T(1), lacc, step);
         if (P.lds_mask) {
             // flush this workgroup's share of the small modes' gradient once
             __syncthreads();
@@ -201,13 +201,15 @@ __global__ void __launch_bounds__(1024) k_fed_sample(const FedArgs<T> F, int j)
     double lacc = 0.0;
     if (P.lds_mask) {
         for (int64_t e = threadIdx.x; e < P.lds_elems; e += blockDim.x) priv[e] = T(0);
-        __syncthreads();
     }
+    for (int b = threadIdx.x; b < P.nb; b += blockDim.x) bcnt[b] = 0;
+    __syncthreads();
     for (int64_t jb = blockIdx.x; jb < P.nblocks; jb += gridDim.x) {
         const int64_t s0 = jb * P.spb;
         const int64_t s_end = std::min<int64_t>(P.n, s0 + P.spb);
         for (int64_t s = s0 + (int64_t)wave * 64; s < s_end; s += (int64_t)nwaves * 64)
-            lg_chunk<T, D, LANES, VEC, SCATTER>(P, s, LANES, lane, priv, bkey, by, s0, true, T(1), lacc, step);
+            lg_chunk<T, D, LANES, VEC, SCATTER>(P, s, LANES, lane, priv, bkey, by, bcnt, s0, true, T(1), lacc,
+                                                step);
         bucket_write_out<T, D>(P, jb, (int)std::min<int64_t>(P.spb, P.n - s0), bkey, by, bcnt, boff);
     }
     if (P.lds_mask) {

@@ -369,8 +369,8 @@ constexpr int owner_in_flight()
 // weight list is given): the MTTKRP step of the non-fused gradient.
 template <typename T, int D, int LANES, int VEC, bool SCATTER>
 __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int passes, int lane, T* priv,
-                                         uint64_t* bkey, T* by, int64_t block_s0, bool tiled, T scale, double& lacc,
-                                         uint64_t step)
+                                         uint64_t* bkey, T* by, int* bcnt, int64_t block_s0, bool tiled, T scale,
+                                         double& lacc, uint64_t step)
 {
     constexpr int U = samples_in_flight(D, (int)sizeof(T), LANES, VEC);
     static_assert(LANES % U == 0, "samples in flight must divide the lanes per sample");
@@ -423,7 +423,15 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
                 for (int k = 0; k < DM; ++k)
                     if (k < dd) P.c_out[s * dd + k] = (int64_t)ci[k];
             }
-            if (tiled) bkey[s - block_s0] = key;
+            if (tiled) {
+                // stage the sample and count it for the sort, behind the draw's
+                // memory latency
+                bkey[s - block_s0] = key;
+#pragma unroll
+                for (int k = 0; k < DM; ++k)
+                    if (k < dd && ((P.bucket_mask >> k) & 1u))
+                        atomicAdd(bcnt + P.bucket_base[k] + (int)(ci[k] >> P.br_shift), 1);
+            }
         }
 #pragma unroll
         for (int k = 0; k < DM; ++k) {
@@ -565,10 +573,11 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
 }
 
 // Bucketed scatter, sampling side: sorts the (key, y) of the workgroup's
-// nvalid staged samples (bkey, by in LDS) by (mode, bucket) into segment
-// list `seg` of the bucket workspace -- count, scan, place -- and records
-// where each bucket starts in the list.  bcnt is LDS scratch of nb ints, boff
-// of nb + 1.  Every thread of the workgroup calls it.
+// nvalid staged samples (bkey, by in LDS), counted by lg_chunk into bcnt, by
+// (mode, bucket) into segment list `seg` of the bucket workspace -- scan,
+// place -- and records where each bucket starts in the list.  boff is LDS
+// scratch of nb + 1 ints; bcnt is zero again when it returns.  Every thread of
+// the workgroup calls it.
 template <typename T, int D>
 __device__ __forceinline__ void bucket_write_out(const LGParams<T>& P, int64_t seg, int nvalid, const uint64_t* bkey,
                                                  const T* by, int* bcnt, int* boff)
@@ -576,21 +585,13 @@ __device__ __forceinline__ void bucket_write_out(const LGParams<T>& P, int64_t s
     constexpr int DM = D > 0 ? D : kMaxModes;
     const int dd = D > 0 ? D : P.sc.d;
     __syncthreads();
-    for (int b = threadIdx.x; b < P.nb; b += blockDim.x) bcnt[b] = 0;
-    __syncthreads();
-    for (int e = threadIdx.x; e < nvalid; e += blockDim.x) {
-        uint32_t ci[DM];
-        unpack_all<D == 0>(P.sc.L, dd, bkey[e], ci);
-#pragma unroll
-        for (int k = 0; k < DM; ++k)
-            if (k < dd && ((P.bucket_mask >> k) & 1u))
-                atomicAdd(bcnt + P.bucket_base[k] + (int)(ci[k] >> P.br_shift), 1);
-    }
-    __syncthreads();
     if ((threadIdx.x >> 6) == 0) wave_exclusive_scan(bcnt, boff, P.nb, threadIdx.x);
     __syncthreads();
     int* start = P.start + seg * (P.nb + 1);
-    for (int b = threadIdx.x; b <= P.nb; b += blockDim.x) start[b] = boff[b];
+    for (int b = threadIdx.x; b <= P.nb; b += blockDim.x) {
+        start[b] = boff[b];
+        if (b < P.nb) bcnt[b] = 0;
+    }
     __syncthreads();
     uint4* out = P.entries + seg * P.entry_cap;
     for (int e = threadIdx.x; e < nvalid; e += blockDim.x) {

@@ -35,8 +35,10 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_
 
     if (SCATTER && P.lds_mask) {
         for (int64_t e = threadIdx.x; e < P.lds_elems; e += blockDim.x) priv[e] = T(0);
-        __syncthreads();
     }
+    if (P.bucket_mask)
+        for (int b = threadIdx.x; b < P.nb; b += blockDim.x) bcnt[b] = 0;
+    if (P.bucket_mask || (SCATTER && P.lds_mask)) __syncthreads();
     const int dd = D > 0 ? D : P.sc.d;
     const int R = P.R;
     const T scale = P.scale ? *P.scale : T(1);
@@ -64,8 +66,8 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_
         const int64_t s_step = (int64_t)(tiled ? nwaves : nwaves * (int)gridDim.x) * B.chunk_samples;
         for (int64_t s0 = b0 + (int64_t)first * B.chunk_samples; s0 < b1; s0 += s_step) {
             const LGParams<T>& Q = params();
-            lg_chunk<T, D, LANES, VEC, SCATTER>(Q, s0, Q.passes, lane, priv, bkey, by, b0, tiled, scale, lacc,
-                                                Q.sc.step);
+            lg_chunk<T, D, LANES, VEC, SCATTER>(Q, s0, Q.passes, lane, priv, bkey, by, bcnt, b0, tiled, scale,
+                                                lacc, Q.sc.step);
         }
         const LGParams<T>& W = params();
         if (tiled && !W.loss_only) bucket_write_out<T, D>(W, j, (int)(b1 - b0), bkey, by, bcnt, boff);

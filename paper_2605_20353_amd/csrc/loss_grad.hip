@@ -283,10 +283,13 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     // each, down to what a lane group keeps in flight at once
     const int groups = 64 / lanes;
     int passes = lanes;
-    if (!bucket_mask)
-        while (passes > samples_in_flight(order, (int)sizeof(T), lanes, vec) &&
-               ceil_div(n, (int64_t)groups * passes) < (int64_t)kWavesPerCu * cus)
-            passes /= 2;
+    const int in_flight = samples_in_flight(order, (int)sizeof(T), lanes, vec);
+    if (!bucket_mask) {
+        while (passes > in_flight && ceil_div(n, (int64_t)groups * passes) < (int64_t)kWavesPerCu * cus) passes /= 2;
+    } else {
+        // sorted blocks of fewer chunks than the workgroup has wavefronts: smaller chunks
+        while (passes > in_flight && spb / (groups * passes) < nwaves) passes /= 2;
+    }
     const int chunk = groups * passes;
     const int64_t nchunks = ceil_div(n, chunk);
     int64_t grid;
