@@ -501,9 +501,14 @@ def _counter_rows(d: str):
     return rows
 
 
+def _flags_as_digits(name: str) -> str:
+    """A kernel's name with its bool template arguments as 0 and 1 (demanglers print either)."""
+    return name.replace("false", "0").replace("true", "1")
+
+
 def _median_counter(rows, counter: str, kernel_sub: str) -> float:
     vals = [float(r["Counter_Value"]) for r in rows
-            if r.get("Counter_Name") == counter and kernel_sub in r.get("Kernel_Name", "")]
+            if r.get("Counter_Name") == counter and kernel_sub in _flags_as_digits(r.get("Kernel_Name", ""))]
     if not vals:
         raise SystemExit(f"no {counter} rows for kernels matching {kernel_sub!r}")
     return float(np.median(vals)), len(vals)
@@ -525,11 +530,11 @@ def traffic_summary(dirs, tile: G.Tile) -> dict:
                                "write_size_kib": cw, "fetch_factor": ff, "write_factor": fw}
     per = {}
     total_r = total_w = 0.0
-    # the exact instantiations of the benchmark's call (SRC = 0: samples drawn
-    # in the kernel; the tile's lane shape)
+    # the exact instantiations of the benchmark's call (0: nothing scattered in
+    # the sampling loop; the tile's lane shape)
     shape = f"3, {tile.lanes}, {tile.vec}"
     for name, match in (("k_loss_grad", f"k_loss_grad<float, {shape}, 0>"),
-                        ("k_bucket_accum", f"k_bucket_accum<float, {shape}>"), ("k_adam", "k_adam<float>")):
+                        ("k_bucket_accum", f"k_bucket_accum<float, {shape}>"), ("k_adam", "k_adam<float")):
         try:
             kf, nd = _median_counter(fetch, "FETCH_SIZE", match)
             kw, _ = _median_counter(write, "WRITE_SIZE", match)

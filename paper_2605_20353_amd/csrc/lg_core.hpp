@@ -361,7 +361,7 @@ constexpr int owner_in_flight()
 // Bound by the draw's random reads (2^21 samples of 10000x8000x6000, 5e7
 // nonzeros: 66 us to draw alone, 81 us with the gathers and the objective
 // where the form that unpacked keys and evaluated losses in every lane and
-// staged samples through LDS took 98 us) and, with sorting, by its stores.
+// staged samples through LDS took 134 us) and, with sorting, by its stores.
 // P.src: 0 draw the samples (the fused sampled gradient); 1 read a
 // materialised list (coordinates, x, w); 2 draw and write the sampled tensor
 // (coordinates and y = w f'(x, m)): the sampling step of the non-fused
