@@ -615,7 +615,8 @@ inline size_t sort_lds_bytes(int spb, int elem_bytes, int nb) { return (size_t)s
 
 // Value that lane IT of each lane group (LANES lanes) holds, in every lane of
 // the group: DPP row broadcasts, one per group of a row of 16 lanes, each
-// written to its group's banks of four lanes; a bpermute for other widths.
+// written to its group's banks of four lanes; lane reads for groups of 32 and
+// 64 (a bpermute would add to the LDS); a bpermute for groups of 2.
 template <int LANES, int IT>
 __device__ __forceinline__ uint32_t group_bcast(uint32_t v, int group_at)
 {
@@ -626,6 +627,11 @@ __device__ __forceinline__ uint32_t group_bcast(uint32_t v, int group_at)
         return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)v, 0x158 + IT, 0xf, 0xc, false);
     } else if constexpr (LANES == 4) {
         return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, IT * 0x55, 0xf, 0xf, true);    // quad_perm
+    } else if constexpr (LANES == 64) {
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, IT);
+    } else if constexpr (LANES == 32) {
+        const int lo = __builtin_amdgcn_readlane((int)v, IT), hi = __builtin_amdgcn_readlane((int)v, 32 + IT);
+        return (uint32_t)(group_at ? hi : lo);
     } else {
         return (uint32_t)__builtin_amdgcn_ds_bpermute(group_at + (IT << 2), (int)v);
     }

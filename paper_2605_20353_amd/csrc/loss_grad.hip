@@ -112,12 +112,19 @@ constexpr int kWavesPerCu = 16;
 // 10 G/s, while about 50 G entries/s go through at rank 32: with 8 per CU at
 // every size, 2^20 samples of a 25000-row mode spent 40 of 49 us on flushes
 // (call 131 us, 110 us with 512 workgroups); 2^21 samples of 24000 rows are
-// indifferent from 768 to 2112 workgroups.
+// indifferent from 768 to 2112 workgroups.  That is for model rows of up to 256
+// bytes (rank 64: indifferent from 750 to 1500); wider ones count as one entry
+// per 128 bytes, since their gathers take as much longer (2^19 samples, rank
+// 200: 491 us a call with 750 workgroups, 451 with 1500; rank 100: 230 with
+// 750, 209 with 3000).
 constexpr int kOwnerEntries = 4096;
+constexpr int kOwnerRowBytes = 128, kOwnerWideRowBytes = 256;
 constexpr int kOwnerWgPerCuMin = 2, kOwnerWgPerCuMax = 8;
 // Threads of an owner workgroup: 512 from this many entries on (2^21 samples of
 // three modes: 210 us a call, 220 us with 1024), below it 1024, whose fewer
-// workgroups flush less (2^17 samples: 29 us, 33 us with 512).
+// workgroups flush less (2^17 samples: 29 us, 33 us with 512), and for wide rows
+// (2^19 samples: rank 100 218 us a call with 512 and 200 with 1024, rank 200
+// 452 and 438).
 constexpr int64_t kOwnerSmallBlockEntries = 1 << 20;
 
 template <typename T>
@@ -373,9 +380,10 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     if (bucket_mask) {
         BAKernel<T> bk = pick_bucket_kernel<T>(order, lanes, vec);
         if (!bk) return set_error(GCP_ERR_UNSUPPORTED, "no bucket kernel for lanes = %d, vec = %d", lanes, vec);
-        const int bblock = (tile && tile->bucket_block > 0)              ? tile->bucket_block
-                           : n * (int64_t)nbm >= kOwnerSmallBlockEntries ? 512
-                                                                         : 1024;
+        const bool wide_rows = P.stride_b > (uint32_t)kOwnerWideRowBytes;
+        const int bblock = (tile && tile->bucket_block > 0)                            ? tile->bucket_block
+                           : n * (int64_t)nbm >= kOwnerSmallBlockEntries && !wide_rows ? 512
+                                                                                       : 1024;
         if (bblock % 64 != 0 || bblock > 1024) return set_error(GCP_ERR_ARG, "bucket_block = %d", bblock);
         const int bwaves = bblock / 64;
         // workgroups per row block: proportional to the entries a row block
@@ -385,9 +393,10 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
         // segment would hold up the workgroup
         const int64_t rows_blk = int64_t(1) << br_shift;
         const double entries = (double)n * nbm;
-        const double per_wg =
-            std::max(1.0, entries / std::max<double>((double)kOwnerWgPerCuMin * cus,
-                                                     std::min<double>((double)kOwnerWgPerCuMax * cus, entries / kOwnerEntries)));
+        const double weight = wide_rows ? (double)P.stride_b / kOwnerRowBytes : 1.0;
+        const double per_wg = std::max(
+            1.0, entries / std::max<double>((double)kOwnerWgPerCuMin * cus,
+                                            std::min<double>((double)kOwnerWgPerCuMax * cus, weight * entries / kOwnerEntries)));
         int64_t wg = 0;
         for (int k = 0; k < d; ++k) {
             P.bwg_base[k] = wg;
