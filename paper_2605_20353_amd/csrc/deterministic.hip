@@ -62,10 +62,12 @@ __global__ void __launch_bounds__(256) k_det_starts(const uint32_t* __restrict__
 }
 
 // Lanes per gradient row in k_det_reduce at VEC columns per lane: enough for R
-// columns, a power of two, at most 64.
+// columns, a power of two, at most 64 and at least 8: a lane holds a pair as
+// well, and a run is read in batches of that many, one after the other (2000
+// samples of 60 rank-8 rows: 173 us a call with groups of 2, 77 with 8).
 __host__ __device__ inline int det_group_lanes(int R, int vec)
 {
-    int rp = 1;
+    int rp = 8;
     while (rp * vec < R && rp < 64) rp <<= 1;
     return rp;
 }
@@ -81,6 +83,8 @@ __device__ __forceinline__ double lane_get(double v, int src)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+constexpr uint32_t kDetLongRun = 512;
+
 // One lane group per gradient row: RP lanes of VEC columns (wider ranks take
 // the columns RP VEC at a time), so a wavefront holds H = 64 / RP rows at once.
 // A group reads its row's run of sorted (row, sample) pairs RP at a time, one
@@ -93,6 +97,12 @@ __device__ __forceinline__ double lane_get(double v, int src)
 // ahead, and U pairs' rows are in flight at once.  16 bytes per lane: a load instruction costs the
 // vector memory path the same whatever its width (2^20 samples, rank 32: 142 us
 // with one column per lane and no read-ahead).
+// A run of kDetLongRun pairs or more is shared by a workgroup (the first
+// long_wgs workgroups look for them): each lane group takes a slice whose
+// bounds the run's length alone fixes, and the slices' sums are added in their
+// order.  (One group walking a row's 10000 pairs is a chain of batches: 2^19
+// samples of a 400x300x200x100x50 tensor at rank 32 took 5.8 ms a call, 0.37
+// with shared runs; 172x25000x300 at rank 100 668 and 250 us.)
 // runs: the rows to visit (those with pairs); NULL visits every row, and rows
 // without pairs get 0 when the call does not accumulate.
 template <typename T, int D, int VEC>
@@ -102,29 +112,38 @@ __global__ void __launch_bounds__(256) k_det_reduce(const uint32_t* __restrict__
                                                     const uint32_t* __restrict__ svals,
                                                     const uint4* __restrict__ rec, const T* __restrict__ A, DetModes M,
                                                     KeyLayout L, int R,
-                                                    const T* __restrict__ scale, int accumulate, T* __restrict__ G)
+                                                    const T* __restrict__ scale, int accumulate, int long_wgs,
+                                                    T* __restrict__ G)
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
     constexpr int DO = DM - 1;
     constexpr int U = D > 0 && DO * VEC * (int)sizeof(T) <= 48 ? 8 : 4;
     const int dd = D > 0 ? D : M.d;
     const int lane = threadIdx.x & 63;
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    const int64_t wave = (((int64_t)blockIdx.x - long_wgs) * blockDim.x + threadIdx.x) >> 6;
+    const int64_t nw = ((int64_t)(gridDim.x - long_wgs) * blockDim.x) >> 6;
     const T sc = scale ? *scale : T(1);
     const int RP = det_group_lanes(R, VEC);
     const int H = 64 / RP;
     const int h = lane / RP, cg = lane % RP, gl0 = h * RP;
     const int64_t nr = runs ? (int64_t)*nruns : (int64_t)rows;
-    for (int64_t j0 = wave * H; j0 < nr; j0 += nw * H) {
-        const int64_t j = j0 + h;
-        if (j >= nr) break;               // no row for this group; shuffles stay inside a group
-        const uint32_t r = runs ? runs[j] : (uint32_t)j;
+    const int gi = (threadIdx.x >> 6) * H + h, groups = 4 * H;
+    __shared__ T part[256 * VEC];
+    __shared__ uint32_t list[256];
+    __shared__ int nlist;
+    // row r by this lane group, or its slice of the run where the workgroup shares the row
+    auto row_sum = [&](uint32_t r, auto shared) {
         int k = 0;
         for (int kk = 1; kk < dd; ++kk)
             if (M.rowoff[kk] <= r) k = kk;
-        const uint32_t b = start[r], e = start[r + 1];
-        if (b == e && accumulate) continue;
+        uint32_t b = start[r], e = start[r + 1];
+        if constexpr (shared.value) {
+            const uint32_t per = (((e - b) + groups - 1) / groups + RP - 1) / RP * RP;
+            b = min(b + (uint32_t)gi * per, e);
+            e = min(b + per, e);
+        } else {
+            if (e - b >= kDetLongRun || (b == e && accumulate)) return;
+        }
         for (int c0 = 0; c0 < R; c0 += RP * VEC) {
             const int c = c0 + cg * VEC;
             const bool col = c < R;
@@ -191,12 +210,43 @@ __global__ void __launch_bounds__(256) k_det_reduce(const uint32_t* __restrict__
                     }
                 }
             }
+            if constexpr (shared.value) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) part[threadIdx.x * VEC + v] = acc[v];
+                __syncthreads();
+                if (gi == 0) {
+                    for (int q = 1; q < groups; ++q)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) acc[v] += part[(q * RP + cg) * VEC + v];
+                }
+                __syncthreads();
+                if (gi != 0) continue;
+            }
             if (col) {
                 T* g = G + (uint64_t)r * (uint32_t)R + c;
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) g[v] = accumulate ? g[v] + acc[v] : acc[v];
             }
         }
+    };
+    if (blockIdx.x < (unsigned)long_wgs) {
+        // rows with long runs, one by one: each thread looks at one row in turn
+        for (int64_t jb = blockIdx.x; jb < nr; jb += (int64_t)long_wgs * 256) {
+            if (threadIdx.x == 0) nlist = 0;
+            __syncthreads();
+            const int64_t j = jb + (int64_t)threadIdx.x * long_wgs;
+            if (j < nr) {
+                const uint32_t r = runs ? runs[j] : (uint32_t)j;
+                if (start[r + 1] - start[r] >= kDetLongRun) list[atomicAdd(&nlist, 1)] = r;
+            }
+            __syncthreads();
+            const int nl = nlist;
+            for (int q = 0; q < nl; ++q) row_sum(list[q], std::true_type{});
+            __syncthreads();
+        }
+    } else {
+        // shuffles stay inside a group, so a group without a row may leave
+        for (int64_t j = wave * H + h; j < nr; j += nw * H) row_sum(runs ? runs[j] : (uint32_t)j, std::false_type{});
     }
 }
 
@@ -361,10 +411,17 @@ gcp_status launch_det(gcp_tensor_s* t, const gcp_sample_params* sp, const void* 
                        : (t->d == 3   ? k_det_reduce<T, 3, 1>
                           : t->d == 4 ? k_det_reduce<T, 4, 1>
                                       : k_det_reduce<T, 0, 1>);
-    hipLaunchKernelGGL(reduce, dim3(rg), dim3(256), 0, stream, (const uint32_t*)(ws + L.start),
+    // workgroups for the long runs: as many as run at once where the rows of the
+    // shortest mode have long runs on average (172x25000x300, 2^19 samples: 250 us
+    // a call, 295 with one per CU), else one per CU to look for the few
+    // (10000x8000x6000, 2^20 samples: 246 us, 262 with four)
+    const int64_t shortest = *std::min_element(t->dims, t->dims + t->d);
+    const int64_t lookers = pairs < (int64_t)kDetLongRun ? 0 : n / shortest >= (int64_t)kDetLongRun / 2 ? cus * 4 : cus;
+    const int long_wgs = (int)std::min<int64_t>(max_runs, lookers);
+    hipLaunchKernelGGL(reduce, dim3(rg + (unsigned)long_wgs), dim3(256), 0, stream, (const uint32_t*)(ws + L.start),
                        listed ? (const uint32_t*)(ws + L.runs) : nullptr, (const uint32_t*)(ws + L.nruns), rows,
                        (const uint32_t*)(ws + L.vals_out), (const uint4*)(ws + L.rec), (const T*)A, M, t->layout, R, (flags & GCP_SCALE_BY_DEV) ? (const T*)scale_dev : nullptr,
-                       accumulate ? 1 : 0, (T*)G_out);
+                       accumulate ? 1 : 0, long_wgs, (T*)G_out);
     GCP_HIP(hipGetLastError());
     // 6. the objective, partials in slot order
     if (loss_out) {
