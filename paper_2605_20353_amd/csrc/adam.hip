@@ -111,10 +111,9 @@ static gcp_status launch_adam(void* A, void* G, void* B, void* C, int64_t n, int
     a.eps = (T)eps;
     a.lower = (T)lower;
     a.zero_grad = (flags & GCP_ADAM_ZERO_GRAD) ? 1 : 0;
-    const int64_t work = ceil_div(n, 16 / (int64_t)sizeof(T));
-    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ceil_div(work, 256), int64_t(1) << 30));
-    if (4 * n * (int64_t)sizeof(T) >= kAdamStreamBytes) k_adam<T, true><<<(unsigned)blocks, 256, 0, stream>>>(a);
-    else k_adam<T, false><<<(unsigned)blocks, 256, 0, stream>>>(a);
+    const unsigned blocks = stream_blocks(ceil_div(n, 16 / (int64_t)sizeof(T)));
+    if (4 * n * (int64_t)sizeof(T) >= kAdamStreamBytes) k_adam<T, true><<<blocks, 256, 0, stream>>>(a);
+    else k_adam<T, false><<<blocks, 256, 0, stream>>>(a);
     GCP_HIP(hipGetLastError());
     return GCP_OK;
 }

@@ -325,6 +325,16 @@ __device__ __forceinline__ void adam_update(T& p, T g, T& b, T& c, T lr, T b1, T
 
 int device_cu_count(int device);
 int64_t ceil_div(int64_t a, int64_t b);
+// Workgroups of a streaming launch of 256-thread workgroups with a thread per
+// item, as many as a launch may have: fewer than 2^32 threads in a dimension
+// (items of 16 bytes reach that at 64 GiB).  The kernels stride over the grid
+// for the rest.
+inline unsigned stream_blocks(int64_t items)
+{
+    const int64_t most = 0xffffffffll / 256;
+    const int64_t blocks = items / 256 + (items % 256 != 0);
+    return (unsigned)(blocks < 1 ? 1 : blocks > most ? most : blocks);
+}
 // Checks a launch's dynamic LDS against the device limit and opts the kernel
 // in to more than 64 KiB when needed.
 gcp_status prepare_lds(const void* fn, size_t bytes, int device);

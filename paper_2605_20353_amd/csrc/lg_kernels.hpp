@@ -161,10 +161,7 @@ __global__ void __launch_bounds__(256) k_zero(T* __restrict__ p, int64_t n, doub
 }
 
 // Workgroups of a k_zero launch over n elements of `bytes` bytes.
-inline unsigned zero_blocks(int64_t n, int bytes)
-{
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n * bytes, 16 * 256), int64_t(1) << 30));
-}
+inline unsigned zero_blocks(int64_t n, int bytes) { return stream_blocks((n * bytes + 15) / 16); }
 
 template <typename T>
 using LGKernel = void (*)(const LGParams<T>);
