@@ -20,6 +20,7 @@
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_select.hpp>
 
+#include "det_runs.hpp"
 #include "lg_kernels.hpp"
 
 namespace gcp {
@@ -138,9 +139,8 @@ __global__ void __launch_bounds__(256) k_det_reduce(const uint32_t* __restrict__
             if (M.rowoff[kk] <= r) k = kk;
         uint32_t b = start[r], e = start[r + 1];
         if constexpr (shared.value) {
-            const uint32_t per = (((e - b) + groups - 1) / groups + RP - 1) / RP * RP;
-            b = min(b + (uint32_t)gi * per, e);
-            e = min(b + per, e);
+            const uint32_t rb = b, re = e;
+            det_slice(rb, re, (uint32_t)groups, (uint32_t)gi, (uint32_t)RP, b, e);
         } else {
             if (e - b >= kDetLongRun || (b == e && accumulate)) return;
         }
@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(256) k_det_reduce(const uint32_t* __restrict__
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[v] = T(0);
             // lane cg of the group: pair i0 + cg (past the run's end: its last pair)
-            auto sample = [&](uint32_t i0) { return svals[min(i0 + (uint32_t)cg, e - 1)]; };
+            auto sample = [&](uint32_t i0) { return svals[det_lane(i0, e, (uint32_t)cg)]; };
             T yl = T(0);
             uint32_t orow[DO], s1 = 0;
             auto pair = [&](uint32_t sl) {
@@ -169,8 +169,8 @@ __global__ void __launch_bounds__(256) k_det_reduce(const uint32_t* __restrict__
                 pair(sample(b));
                 s1 = sample(b + (uint32_t)RP);
             }
-            for (uint32_t i0 = b; i0 < e; i0 += (uint32_t)RP) {
-                const uint32_t nv = min(e - i0, (uint32_t)RP);
+            for (uint32_t i0 = b, nv; i0 < e; i0 += nv) {
+                nv = det_batch(i0, e, (uint32_t)RP);
                 const T yc = yl;
                 uint32_t oc[DO];
 #pragma unroll
