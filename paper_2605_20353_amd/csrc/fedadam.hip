@@ -671,7 +671,10 @@ static gcp_status fed_build(gcp_fed_s* f)
     memcpy(f->args, &a, sizeof(a));
 
     bool order3 = d == 3;
-    for (const gcp_fed_client& cl : f->clients) order3 = order3 && kernel_order(cl.tensor, R, f->bucketed) == 3;
+    for (const gcp_fed_client& cl : f->clients) {
+        const KernelOrder o = kernel_order(cl.tensor, R, f->bucketed);
+        order3 = order3 && o.order == 3 && !o.wide;
+    }
     if (D.batched && f->bucketed) {
         const bool scatter = bucket_mask != (1u << d) - 1;   // some mode is LDS-private or atomic
         FedStepKernel<T> sk = order3 ? pick_fed_sample<T, 3>(scatter, f->lanes, f->vec)

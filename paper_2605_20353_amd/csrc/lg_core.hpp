@@ -367,7 +367,7 @@ constexpr int owner_in_flight()
 // (coordinates and y = w f'(x, m)): the sampling step of the non-fused
 // gradient; 3 read a sampled tensor whose values are already y (w = 1 unless a
 // weight list is given): the MTTKRP step of the non-fused gradient.
-template <typename T, int D, int LANES, int VEC, bool SCATTER>
+template <typename T, int D, int LANES, int VEC, bool SCATTER, bool WIDE = false>
 __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int passes, int lane, T* priv,
                                          uint64_t* bkey, T* by, int* bcnt, int64_t block_s0, bool tiled, T scale,
                                          double& lacc, uint64_t step)
@@ -375,6 +375,7 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
     constexpr int U = samples_in_flight(D, (int)sizeof(T), LANES, VEC);
     static_assert(LANES % U == 0, "samples in flight must divide the lanes per sample");
     constexpr int DM = D > 0 ? D : kMaxModes;
+    constexpr bool BYTES = D > 0 && !WIDE;   // rows by 32-bit byte offsets, else by index
     const int dd = D > 0 ? D : P.sc.d;
     const int R = P.R;
     const int g = lane / LANES, cl = lane % LANES;
@@ -387,7 +388,7 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
     const int64_t s = s0 + g * passes + cl;
     const bool mine = cl < passes && s < P.n;
     uint64_t key = 0;
-    uint32_t off[DM];                      // D > 0: byte offset of the row in A; else its row index
+    uint32_t off[DM];                      // BYTES: byte offset of the row in A; else its index
     T x = T(0), w = T(0);
     {
         uint32_t ci[DM];
@@ -435,7 +436,7 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
         }
 #pragma unroll
         for (int k = 0; k < DM; ++k) {
-            if constexpr (D > 0) off[k] = P.rowb[k] + ci[k] * P.stride_b;
+            if constexpr (BYTES) off[k] = P.rowb[k] + ci[k] * P.stride_b;
             else off[k] = (uint32_t)P.rowoff[k] + ci[k];
         }
     }
@@ -458,7 +459,7 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
 #pragma unroll
                 for (int k = 0; k < DM; ++k) {
                     if (k < dd) {
-                        if constexpr (D > 0)
+                        if constexpr (BYTES)
                             load_cols<T, VEC>(reinterpret_cast<const T*>(reinterpret_cast<const char*>(P.A) +
                                                                          (o[u][k] + colb)),
                                               a[u][k]);
@@ -535,7 +536,7 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
                     for (int k = DM - 1; k >= 0; --k) {
                         if (k < dd && !((P.bucket_mask >> k) & 1u)) {
                             if ((P.lds_mask >> k) & 1u) {
-                                if constexpr (D > 0)
+                                if constexpr (BYTES)
                                     lds_add_cols<T, VEC>(reinterpret_cast<T*>(reinterpret_cast<char*>(priv) +
                                                                               (o[u][k] + colb + P.ldsb[k])),
                                                          cv[k]);
@@ -545,7 +546,7 @@ __device__ __forceinline__ void lg_chunk(const LGParams<T>& P, int64_t s0, int p
                                                          cv[k]);
                             } else {
                                 T* dst;
-                                if constexpr (D > 0)
+                                if constexpr (BYTES)
                                     dst = reinterpret_cast<T*>(reinterpret_cast<char*>(P.G) + (o[u][k] + colb));
                                 else
                                     dst = P.G + row_elem(o[u][k], R) + col0;
@@ -671,7 +672,7 @@ __device__ __forceinline__ void static_for(F&& f)
 // and a broadcast by bpermute adds to the LDS, which the adds fill.)  The next
 // batch's entries are in flight while a batch is worked on.  Every thread of
 // the workgroup calls it; part is complete when it returns.
-template <typename T, int D, int LANES, int VEC>
+template <typename T, int D, int LANES, int VEC, bool WIDE = false>
 __device__ __forceinline__ void bucket_accumulate(const LGParams<T>& P, int k, int b, int64_t r0, int64_t rows,
                                                   int64_t j0, int64_t j1, T* part)
 {
@@ -679,6 +680,7 @@ __device__ __forceinline__ void bucket_accumulate(const LGParams<T>& P, int k, i
     constexpr int U = owner_in_flight<T, D, LANES, VEC>();
     constexpr int DM = D > 0 ? D : kMaxModes;
     constexpr int DO = DM - 1;
+    constexpr bool BYTES = D > 0 && !WIDE;     // rows by 32-bit byte offsets, else by index
     static_assert(D == 0 || D >= 2, "orders with their own kernels");
     const int nwaves = blockDim.x >> 6;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -733,7 +735,7 @@ __device__ __forceinline__ void bucket_accumulate(const LGParams<T>& P, int k, i
             const int nb = min(64, total - t);
             const uint64_t key = (uint64_t)nxt.x | ((uint64_t)nxt.y << 32);
             const T y = entry_y<T>(nxt);
-            uint32_t off[DO];                          // D > 0: byte offset of the row in A; else its row index
+            uint32_t off[DO];                          // BYTES: byte offset of the row in A; else its index
             uint32_t loc;                              // byte offset of the entry's row in part
             {
                 uint32_t ci[DM];
@@ -748,7 +750,7 @@ __device__ __forceinline__ void bucket_accumulate(const LGParams<T>& P, int k, i
                 for (int o = 0; o < DO; ++o) {
                     const bool after = o >= k;
                     const uint32_t i = after ? ci[o + 1] : ci[o];
-                    if constexpr (D > 0) off[o] = (after ? P.rowb[o + 1] : P.rowb[o]) + i * P.stride_b;
+                    if constexpr (BYTES) off[o] = (after ? P.rowb[o + 1] : P.rowb[o]) + i * P.stride_b;
                     else off[o] = (uint32_t)(after ? P.rowoff[o + 1] : P.rowoff[o]) + i;
                 }
             }
@@ -762,7 +764,7 @@ __device__ __forceinline__ void bucket_accumulate(const LGParams<T>& P, int k, i
                         for (int o = 0; o < DO; ++o) {
                             if (D > 0 || o < dd - 1) {
                                 const uint32_t ro = group_bcast<LANES, it0 + u>(off[o], group_at);
-                                if constexpr (D > 0)
+                                if constexpr (BYTES)
                                     load_cols<T, VEC>(reinterpret_cast<const T*>(
                                                           reinterpret_cast<const char*>(P.A) + (ro + colb)),
                                                       a[u][o]);

@@ -3,5 +3,5 @@
 #include "lg_kernels.hpp"
 
 namespace gcp {
-GCP_LG_INSTANTIATE(float, 4)
+GCP_LG_INSTANTIATE(float, 4, false)
 }

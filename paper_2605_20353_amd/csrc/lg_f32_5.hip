@@ -3,5 +3,5 @@
 #include "lg_kernels.hpp"
 
 namespace gcp {
-GCP_LG_INSTANTIATE(float, 5)
+GCP_LG_INSTANTIATE(float, 5, false)
 }

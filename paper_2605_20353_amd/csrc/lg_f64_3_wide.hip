@@ -1,0 +1,7 @@
+// The sampled loss/gradient kernels in double, order 3, for models of 4 GiB and
+// more: a translation unit of their own, so that they build in parallel.
+#include "lg_kernels.hpp"
+
+namespace gcp {
+GCP_LG_INSTANTIATE(double, 3, true)
+}

@@ -3,5 +3,5 @@
 #include "lg_kernels.hpp"
 
 namespace gcp {
-GCP_LG_INSTANTIATE(double, 5)
+GCP_LG_INSTANTIATE(double, 5, false)
 }

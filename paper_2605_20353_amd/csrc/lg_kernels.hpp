@@ -13,14 +13,15 @@ namespace gcp {
 // Wavefronts per SIMD the register allocation aims at: the float kernels that
 // scatter nothing in their loop fit 64 VGPRs (68-76 unconstrained), and with 8
 // resident the bucketed launch's workgroups all start at once.
-template <typename T, int D, bool SCATTER>
+template <typename T, int D, bool SCATTER, bool WIDE>
 constexpr int lg_min_waves()
 {
-    return sizeof(T) == 4 && !SCATTER && D > 0 ? 8 : 4;
+    return sizeof(T) == 4 && !SCATTER && D > 0 && !WIDE ? 8 : 4;
 }
 
-template <typename T, int D, int LANES, int VEC, bool SCATTER>
-__global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_grad(const LGParams<T> P)
+// WIDE: a model of 4 GiB or more, whose rows are found by 64-bit products.
+template <typename T, int D, int LANES, int VEC, bool SCATTER, bool WIDE>
+__global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER, WIDE>())) k_loss_grad(const LGParams<T> P)
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -66,7 +67,7 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_
         const int64_t s_step = (int64_t)(tiled ? nwaves : nwaves * (int)gridDim.x) * B.chunk_samples;
         for (int64_t s0 = b0 + (int64_t)first * B.chunk_samples; s0 < b1; s0 += s_step) {
             const LGParams<T>& Q = params();
-            lg_chunk<T, D, LANES, VEC, SCATTER>(Q, s0, Q.passes, lane, priv, bkey, by, bcnt, b0, tiled, scale,
+            lg_chunk<T, D, LANES, VEC, SCATTER, WIDE>(Q, s0, Q.passes, lane, priv, bkey, by, bcnt, b0, tiled, scale,
                                                 lacc, Q.sc.step);
         }
         const LGParams<T>& W = params();
@@ -115,8 +116,8 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER>())) k_loss_
 // workgroups [j0, j1) of the sampling launch: per entry it gathers the other
 // modes' rows, forms y prod_{n != k} A_n[i_n, :] and adds it to the LDS copy
 // of its rows; the block is flushed to G once.
-template <typename T, int D, int LANES, int VEC>
-__global__ void __launch_bounds__(1024, (sizeof(T) == 4 && D > 0 ? 8 : 4)) k_bucket_accum(const LGParams<T> P)
+template <typename T, int D, int LANES, int VEC, bool WIDE>
+__global__ void __launch_bounds__(1024, (sizeof(T) == 4 && D > 0 && !WIDE ? 8 : 4)) k_bucket_accum(const LGParams<T> P)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T* part = reinterpret_cast<T*>(smem);
@@ -138,7 +139,7 @@ __global__ void __launch_bounds__(1024, (sizeof(T) == 4 && D > 0 ? 8 : 4)) k_buc
     // waves per workgroup); the last split takes the remainder
     const int64_t j0 = (int64_t)split * P.bsegs[k];
     const int64_t j1 = std::min<int64_t>(P.nblocks, j0 + P.bsegs[k]);
-    bucket_accumulate<T, D, LANES, VEC>(P, k, b, r0, rows, j0, j1, part);
+    bucket_accumulate<T, D, LANES, VEC, WIDE>(P, k, b, r0, rows, j0, j1, part);
     T* dst = P.G + (P.rowoff[k] + r0) * R;
     for (int64_t e = threadIdx.x; e < rows * R; e += blockDim.x) {
         const T v = part[e];
@@ -173,11 +174,12 @@ using BAKernel = void (*)(const LGParams<T>);
     X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(4, 2) X(8, 2) X(16, 2) X(32, 2) X(64, 2) X(2, 4) X(4, 4) X(8, 4) X(16, 4) X(32, 4) X(64, 4)
 #define GCP_LG_SHAPES_F64(X) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(4, 2) X(8, 2) X(16, 2) X(32, 2) X(64, 2) X(64, 4)
 
-template <typename T, int D>
+template <typename T, int D, bool WIDE>
 inline LGKernel<T> pick_shape(bool scatter, int lanes, int vec)
 {
-#define GCP_CASE(LN, VC) \
-    if (lanes == LN && vec == VC) return scatter ? k_loss_grad<T, D, LN, VC, true> : k_loss_grad<T, D, LN, VC, false>;
+#define GCP_CASE(LN, VC)        \
+    if (lanes == LN && vec == VC) \
+        return scatter ? k_loss_grad<T, D, LN, VC, true, WIDE> : k_loss_grad<T, D, LN, VC, false, WIDE>;
     if constexpr (sizeof(T) == 4) {
         GCP_LG_SHAPES_F32(GCP_CASE)
     } else {
@@ -187,11 +189,11 @@ inline LGKernel<T> pick_shape(bool scatter, int lanes, int vec)
     return nullptr;
 }
 
-template <typename T, int D>
+template <typename T, int D, bool WIDE>
 inline BAKernel<T> pick_bucket_shape(int lanes, int vec)
 {
 #define GCP_CASE(LN, VC) \
-    if (lanes == LN && vec == VC) return k_bucket_accum<T, D, LN, VC>;
+    if (lanes == LN && vec == VC) return k_bucket_accum<T, D, LN, VC, WIDE>;
     if constexpr (sizeof(T) == 4) {
         GCP_LG_SHAPES_F32(GCP_CASE)
     } else {
@@ -203,28 +205,29 @@ inline BAKernel<T> pick_bucket_shape(int lanes, int vec)
 
 // The kernels of order D (0: any order) at a lane shape, null when the shape
 // is not built.  scatter: the kernel that scatters in its loop (some mode is
-// LDS-private or atomic).
-template <typename T, int D>
+// LDS-private or atomic).  WIDE is built for orders 3 and 4 (order 0 has
+// 64-bit products anyway).
+template <typename T, int D, bool WIDE>
 LGKernel<T> loss_grad_kernel(bool scatter, int lanes, int vec);
-template <typename T, int D>
+template <typename T, int D, bool WIDE>
 BAKernel<T> bucket_kernel(int lanes, int vec);
 
-#define GCP_LG_INSTANTIATE(T, D)                                         \
-    template <>                                                          \
-    LGKernel<T> loss_grad_kernel<T, D>(bool scatter, int lanes, int vec) \
-    {                                                                    \
-        return pick_shape<T, D>(scatter, lanes, vec);                    \
-    }                                                                    \
-    template <>                                                          \
-    BAKernel<T> bucket_kernel<T, D>(int lanes, int vec)                  \
-    {                                                                    \
-        return pick_bucket_shape<T, D>(lanes, vec);                      \
+#define GCP_LG_INSTANTIATE(T, D, WIDE)                                         \
+    template <>                                                                \
+    LGKernel<T> loss_grad_kernel<T, D, WIDE>(bool scatter, int lanes, int vec) \
+    {                                                                          \
+        return pick_shape<T, D, WIDE>(scatter, lanes, vec);                    \
+    }                                                                          \
+    template <>                                                                \
+    BAKernel<T> bucket_kernel<T, D, WIDE>(int lanes, int vec)                  \
+    {                                                                          \
+        return pick_bucket_shape<T, D, WIDE>(lanes, vec);                      \
     }
 
-#define GCP_LG_DECLARE(T, D)                                              \
-    template <>                                                           \
-    LGKernel<T> loss_grad_kernel<T, D>(bool scatter, int lanes, int vec); \
-    template <>                                                           \
-    BAKernel<T> bucket_kernel<T, D>(int lanes, int vec);
+#define GCP_LG_DECLARE(T, D, WIDE)                                              \
+    template <>                                                                 \
+    LGKernel<T> loss_grad_kernel<T, D, WIDE>(bool scatter, int lanes, int vec); \
+    template <>                                                                 \
+    BAKernel<T> bucket_kernel<T, D, WIDE>(int lanes, int vec);
 
 }  // namespace gcp

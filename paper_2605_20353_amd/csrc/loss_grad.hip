@@ -33,34 +33,38 @@
 
 namespace gcp {
 
-GCP_LG_DECLARE(float, 3)
-GCP_LG_DECLARE(float, 4)
-GCP_LG_DECLARE(float, 5)
-GCP_LG_DECLARE(float, 0)
-GCP_LG_DECLARE(double, 3)
-GCP_LG_DECLARE(double, 4)
-GCP_LG_DECLARE(double, 5)
-GCP_LG_DECLARE(double, 0)
+GCP_LG_DECLARE(float, 3, false)
+GCP_LG_DECLARE(float, 4, false)
+GCP_LG_DECLARE(float, 5, false)
+GCP_LG_DECLARE(float, 0, false)
+GCP_LG_DECLARE(float, 3, true)
+GCP_LG_DECLARE(float, 4, true)
+GCP_LG_DECLARE(double, 3, false)
+GCP_LG_DECLARE(double, 4, false)
+GCP_LG_DECLARE(double, 5, false)
+GCP_LG_DECLARE(double, 0, false)
+GCP_LG_DECLARE(double, 3, true)
+GCP_LG_DECLARE(double, 4, true)
 
 template <typename T>
-static LGKernel<T> pick_kernel(int order, bool scatter, int lanes, int vec)
+static LGKernel<T> pick_kernel(KernelOrder o, bool scatter, int lanes, int vec)
 {
-    switch (order) {
-    case 3: return loss_grad_kernel<T, 3>(scatter, lanes, vec);
-    case 4: return loss_grad_kernel<T, 4>(scatter, lanes, vec);
-    case 5: return loss_grad_kernel<T, 5>(scatter, lanes, vec);
-    default: return loss_grad_kernel<T, 0>(scatter, lanes, vec);
+    switch (o.order) {
+    case 3: return o.wide ? loss_grad_kernel<T, 3, true>(scatter, lanes, vec) : loss_grad_kernel<T, 3, false>(scatter, lanes, vec);
+    case 4: return o.wide ? loss_grad_kernel<T, 4, true>(scatter, lanes, vec) : loss_grad_kernel<T, 4, false>(scatter, lanes, vec);
+    case 5: return loss_grad_kernel<T, 5, false>(scatter, lanes, vec);
+    default: return loss_grad_kernel<T, 0, false>(scatter, lanes, vec);
     }
 }
 
 template <typename T>
-static BAKernel<T> pick_bucket_kernel(int order, int lanes, int vec)
+static BAKernel<T> pick_bucket_kernel(KernelOrder o, int lanes, int vec)
 {
-    switch (order) {
-    case 3: return bucket_kernel<T, 3>(lanes, vec);
-    case 4: return bucket_kernel<T, 4>(lanes, vec);
-    case 5: return bucket_kernel<T, 5>(lanes, vec);
-    default: return bucket_kernel<T, 0>(lanes, vec);
+    switch (o.order) {
+    case 3: return o.wide ? bucket_kernel<T, 3, true>(lanes, vec) : bucket_kernel<T, 3, false>(lanes, vec);
+    case 4: return o.wide ? bucket_kernel<T, 4, true>(lanes, vec) : bucket_kernel<T, 4, false>(lanes, vec);
+    case 5: return bucket_kernel<T, 5, false>(lanes, vec);
+    default: return bucket_kernel<T, 0, false>(lanes, vec);
     }
 }
 
@@ -258,10 +262,10 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     if (R % vec != 0) return set_error(GCP_ERR_ARG, "vec = %d does not divide R = %d", vec, R);
     if (lanes * vec < R) return set_error(GCP_ERR_ARG, "lanes*vec = %d < R = %d", lanes * vec, R);
     const int src = write_y ? 2 : smp ? (given_values ? 3 : 1) : 0;
-    const int order = kernel_order(t, R, bucket_mask != 0);
+    const KernelOrder order = kernel_order(t, R, bucket_mask != 0);
     // the general-order float64 kernel with 64 lanes of one column needs 128
     // VGPRs and spills; even R takes 32 lanes of two columns instead
-    if (sizeof(T) == 8 && order == 0 && lanes == 64 && vec == 1 && R % 2 == 0 && !(tile && tile->lanes > 0)) {
+    if (sizeof(T) == 8 && order.order == 0 && lanes == 64 && vec == 1 && R % 2 == 0 && !(tile && tile->lanes > 0)) {
         lanes = 32;
         vec = 2;
     }
@@ -290,7 +294,7 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     // each, down to what a lane group keeps in flight at once
     const int groups = 64 / lanes;
     int passes = lanes;
-    const int in_flight = samples_in_flight(order, (int)sizeof(T), lanes, vec);
+    const int in_flight = samples_in_flight(order.order, (int)sizeof(T), lanes, vec);
     if (!bucket_mask) {
         while (passes > in_flight && ceil_div(n, (int64_t)groups * passes) < (int64_t)kWavesPerCu * cus) passes /= 2;
     } else {
