@@ -10,13 +10,17 @@
 
 namespace gcp {
 
-// Wavefronts per SIMD the register allocation aims at: the float kernels that
-// scatter nothing in their loop fit 64 VGPRs (68-76 unconstrained), and with 8
-// resident the bucketed launch's workgroups all start at once.
+// Wavefronts per SIMD the register allocation aims at: 8 (64 VGPRs) for the
+// float kernels of orders 3 and 4 that scatter nothing in their loop and for
+// their owner pass, which fit them (68-76 unconstrained; four owner shapes
+// spill one or two), 6 (80 VGPRs) for those of order 5, where up to 14 registers
+// spill at 8 (five-way 400x300x200x100x50:
+// the objective of 2^18 samples at rank 32 23.1 us at 8, 19.2 at 6, 19.5 at 4;
+// 2^20 samples at rank 20, all modes bucketed, 256, 240 and 240 us).
 template <typename T, int D, bool SCATTER, bool WIDE>
 constexpr int lg_min_waves()
 {
-    return sizeof(T) == 4 && !SCATTER && D > 0 && !WIDE ? 8 : 4;
+    return sizeof(T) == 4 && !SCATTER && D > 0 && !WIDE ? (D == 5 ? 6 : 8) : 4;
 }
 
 // WIDE: a model of 4 GiB or more, whose rows are found by 64-bit products.
@@ -117,7 +121,7 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER, WIDE>())) k
 // modes' rows, forms y prod_{n != k} A_n[i_n, :] and adds it to the LDS copy
 // of its rows; the block is flushed to G once.
 template <typename T, int D, int LANES, int VEC, bool WIDE>
-__global__ void __launch_bounds__(1024, (sizeof(T) == 4 && D > 0 && !WIDE ? 8 : 4)) k_bucket_accum(const LGParams<T> P)
+__global__ void __launch_bounds__(1024, (lg_min_waves<T, D, false, WIDE>())) k_bucket_accum(const LGParams<T> P)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T* part = reinterpret_cast<T*>(smem);

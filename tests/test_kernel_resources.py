@@ -64,3 +64,11 @@ def test_double_scattering_kernels(spills, order, vec):
         key = LOSS_GRAD.format(t="d", order=order, lanes=lanes, vec=vec, scatter=1, wide=0)
         found = [n for name, n in spills.items() if key in name]
         assert len(found) == 1 and found[0] <= DOUBLE_LIMITS[order, vec], (key, found)
+
+
+@pytest.mark.parametrize("order", [3, 4, 5])
+def test_float_kernels_that_scatter_nothing(spills, order):
+    # bounded to a number of wavefronts per SIMD that their registers fit
+    for key in ("k_loss_gradIfLi%dELi\\d+ELi\\dELb0ELb0EE" % order, "k_bucket_accumIfLi%dELi\\d+ELi\\dELb0EE" % order):
+        found = {name: n for name, n in spills.items() if re.search(key, name)}
+        assert len(found) == 15 and max(found.values()) <= 2, found
