@@ -150,11 +150,6 @@ __host__ __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1
 {
     constexpr uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
     constexpr uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
-#if defined(__HIP_DEVICE_COMPILE__)
-    // the key schedule stays with the rounds: hoisted out of a sample loop, its
-    // twenty 64-bit words would not fit the scalar registers and spill
-    asm volatile("" : "+s"(k0), "+s"(k1));
-#endif
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         uint64_t hi0, lo0, hi1, lo1;
