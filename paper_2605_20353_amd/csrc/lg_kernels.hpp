@@ -29,6 +29,18 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER, WIDE>())) k
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    // One word of each cache line of the parameter block, all at once: the loops
+    // below read it phase by phase, and each phase's first read waited for a cold
+    // line of its own (32768 uniform samples of a dense 400x300x200 tensor at
+    // rank 32 22.7 us, 20.6 with the lines read ahead).
+    {
+        using Words = const __attribute__((address_space(4))) uint32_t*;
+        const Words words = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+        uint32_t any = 0;
+#pragma unroll
+        for (unsigned i = 0; i < sizeof(LGParams<T>) / 4; i += 16) any |= words[i];
+        asm volatile("" ::"s"(any));
+    }
     const int nwaves = blockDim.x >> 6;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     T* priv = reinterpret_cast<T*>(smem);
