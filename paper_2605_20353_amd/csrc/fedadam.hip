@@ -145,8 +145,8 @@ __global__ void __launch_bounds__(1024) k_fed_clients(const FedArgs<T> F)
             for (int64_t e = threadIdx.x; e < P.lds_elems; e += blockDim.x) priv[e] = T(0);
             __syncthreads();
         }
-        for (int64_t chunk = (int64_t)w * nwaves + wave; chunk < P.nchunks; chunk += (int64_t)F.W * nwaves)
-            lg_chunk<T, D, LANES, VEC, true>(P, chunk * 64, LANES, lane, priv, nullptr, nullptr, nullptr, 0, false,
+        for (int64_t s0 = ((int64_t)w * nwaves + wave) * 64; s0 < P.n; s0 += (int64_t)F.W * nwaves * 64)
+            lg_chunk<T, D, LANES, VEC, true>(P, s0, LANES, lane, priv, nullptr, nullptr, nullptr, 0, false,
                                              T(1), lacc, step);
         if (P.lds_mask) {
             // flush this workgroup's share of the small modes' gradient once
@@ -567,7 +567,6 @@ static gcp_status fed_build(gcp_fed_s* f)
         gcp_status st = make_sample_ctx<T>(t, &sp, h.P.sc, n);
         if (st != GCP_OK) return st;
         h.P.n = n;
-        h.P.nchunks = ceil_div(n, 64);
         h.P.A = (const T*)cl.M;
         h.P.G = (T*)cl.G;
         h.P.R = R;
@@ -585,7 +584,6 @@ static gcp_status fed_build(gcp_fed_s* f)
         set_row_offsets(h.P, t);
         if (bucket_mask) {
             h.P.bucket_mask = bucket_mask;
-            h.P.n_bucket_modes = nbm;
             h.P.br_shift = br_shift;
             h.P.nb = nb_c[c];
             h.P.spb = spb;

@@ -220,17 +220,16 @@ __host__ __device__ __forceinline__ uint64_t divmod_u64_u32(uint64_t n, uint32_t
 }
 
 // Key term of coordinate c of mode k; a cell's key is the sum of its terms.
-// Code built with RADIX = false handles bit-packed layouts only (see unpack_all).
-template <bool RADIX = true>
 __host__ __device__ __forceinline__ uint64_t pack_coord(const KeyLayout& L, uint64_t c, int k)
 {
-    return (RADIX && L.radix) ? c * L.stride[k] : c << L.shift[k];
+    return L.radix ? c * L.stride[k] : c << L.shift[k];
 }
 
 // All coordinates of a key (modes 0 .. dd-1 of at most DM).  Only code built
-// with RADIX = true reads mixed-radix keys: tensors whose layout is mixed
-// radix run the general-order kernels, so the order-specialised ones carry no
-// division code (and none of its registers).
+// with RADIX = true reads mixed-radix keys: drawing a stored nonzero, the
+// bit-reproducible form and the general-order sort and owner pass.  Those of the
+// specialised orders, which mixed-radix keys never reach, carry no division code
+// (and none of its registers).
 template <bool RADIX, int DM>
 __host__ __device__ __forceinline__ void unpack_all(const KeyLayout& L, int dd, uint64_t key, uint32_t (&c)[DM])
 {
@@ -290,8 +289,7 @@ __device__ __forceinline__ bool table_contains(const uint64_t* __restrict__ tabl
 // ------------------------------------------------------------------ losses --
 
 // Internal loss code of the sampled MTTKRP over a given sampled tensor: its
-// values are already the derivative values, so y = w x (the kernels take
-// that branch at compile time).
+// values are already the derivative values, so y = w x.
 constexpr int kLossGivenValues = 3;
 
 template <typename T>

@@ -13,7 +13,6 @@ template <typename T>
 struct LGParams {
     SampleCtx<T> sc;
     int64_t n;            // samples p + q
-    int64_t nchunks;      // ceil(n / chunk_samples)
     const int64_t* m_coords;  // materialised list (src = 1, 3)
     const T* m_x;
     const T* m_w;
@@ -27,7 +26,6 @@ struct LGParams {
     uint32_t rowb[kMaxModes];       // order-specific kernels: byte offset of each mode's first row (models below 4 GiB)
     uint32_t ldsb[kMaxModes];       // the same, from a row's byte offset in A to its LDS-private copy (modulo 2^32)
     int loss;
-    int loss_only;
     int semi;             // semi-stratified: samples s < p get f'(x,m) - f'(0,m)
     const T* scale;       // nullable device scalar
     double* loss_out;     // nullable
@@ -37,13 +35,12 @@ struct LGParams {
     int64_t lds_elems;
     // bucketed scatter
     uint32_t bucket_mask;      // modes scattered through row-block buckets
-    int n_bucket_modes;
     int br_shift;              // rows per bucket = 1 << br_shift
     int nb;                    // buckets over all bucketed modes
     int bucket_base[kMaxModes + 1];
     int spb;                   // samples per workgroup (tiled launch)
     int64_t nblocks;           // workgroups of the tiled launch (J)
-    int64_t entry_cap;         // entries per workgroup segment list = spb * n_bucket_modes
+    int64_t entry_cap;         // entries per workgroup segment list = spb * bucketed modes
     int bucket_lds;            // byte offset of the bucket staging in LDS
     uint4* entries;            // [J][entry_cap] 16-byte {key, y}
     int* start;                // [J][nb + 1] first entry of each bucket in the workgroup's list, then their number
@@ -54,8 +51,7 @@ struct LGParams {
     int bsegs[kMaxModes];
     // non-fused sampling step (src = 2): each sample's y, the sampled
     // tensor's values, and its coordinates [n x d], written instead of
-    // scattering (last, so that the fields above keep their kernel-argument
-    // offsets)
+    // scattering
     T* y_out;
     int64_t* c_out;
     // or, for the deterministic form, both in one 16-byte {key, y} a sample

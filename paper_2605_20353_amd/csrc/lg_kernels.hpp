@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER, WIDE>())) k
                                                 lacc, Q.sc.step);
         }
         const LGParams<T>& W = params();
-        if (tiled && !W.loss_only) bucket_write_out<T, D>(W, j, (int)(b1 - b0), bkey, by, bcnt, boff);
+        if (tiled) bucket_write_out<T, D>(W, j, (int)(b1 - b0), bkey, by, bcnt, boff);
         j += gridDim.x;
         if (!SCATTER || !tiled || j >= W.nblocks) break;
     }

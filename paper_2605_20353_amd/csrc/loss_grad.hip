@@ -325,7 +325,6 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     }
 
     P.n = n;
-    P.nchunks = nchunks;
     if (smp) {
         P.m_coords = smp->coords;
         P.m_x = (const T*)smp->x;
@@ -335,7 +334,6 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     P.G = (T*)G_out;
     P.R = R;
     P.loss = loss;
-    P.loss_only = loss_only;
     P.semi = sp->kind == GCP_SAMPLE_SEMI_STRATIFIED;
     P.scale = (flags & GCP_SCALE_BY_DEV) ? (const T*)scale_dev : nullptr;
     P.loss_out = loss_out;
@@ -359,7 +357,6 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
     P.lds_elems = lds_elems;
     set_row_offsets(P, t);
     P.bucket_mask = bucket_mask;
-    P.n_bucket_modes = nbm;
     P.br_shift = br_shift;
     P.nb = nb;
     P.spb = spb;

@@ -35,7 +35,7 @@ class Case:
                           self.dtype, what=what)
 
 
-# (dtype, rank): 4, 8, 16 lanes and the widths that go by bpermute (2, 32, 64)
+# (dtype, rank): 4, 8 and 16 lanes (DPP), 32 and 64 (lane reads), 2 (bpermute)
 SHAPES = [(torch.float32, 8), (torch.float32, 16), (torch.float32, 32), (torch.float32, 20), (torch.float32, 64),
           (torch.float32, 96), (torch.float32, 33), (torch.float64, 6), (torch.float64, 24), (torch.float64, 48),
           (torch.float64, 5)]
