@@ -25,6 +25,7 @@
 #include <new>
 #include <vector>
 
+#include "fed_owner.hpp"
 #include "lg_core.hpp"
 
 namespace gcp {
@@ -686,17 +687,24 @@ static gcp_status fed_build(gcp_fed_s* f)
         if (st != GCP_OK) return st;
         st = prepare_lds(f->owner_kernel, f->owner_lds, f->device);
         if (st != GCP_OK) return st;
-        // owner workgroups: 1024 threads, fewer when that lets all of them start
-        // at once (16 clients of 5000 x 5000 x 500 blocks: 640 workgroups on
-        // 512 places leave a second, nearly empty wave)
-        for (int threads = 1024; threads >= 256; threads /= 2) {
-            int per_cu = 0;
-            GCP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f->owner_kernel, threads, f->owner_lds));
-            if ((int64_t)K * f->nb_max <= (int64_t)per_cu * device_cu_count(f->device)) {
-                f->owner_block = threads;
-                break;
+        int64_t blocks = 0, places[3];
+        double total = 0.0, largest = 0.0;
+        for (int c = 0; c < K; ++c) {
+            blocks += nb_c[c];
+            total += (double)(D.p + D.q) * nbm;
+            for (int k = 0; k < d; ++k) {
+                const int64_t rows = f->clients[c].tensor->dims[k];
+                if ((bucket_mask >> k) & 1u)
+                    largest = std::max(largest, (double)(D.p + D.q) *
+                                                    (double)std::min<int64_t>(rows, int64_t(1) << br_shift) / (double)rows);
             }
         }
+        for (int i = 0; i < 3; ++i) {
+            int per_cu = 0;
+            GCP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f->owner_kernel, 1024 >> i, f->owner_lds));
+            places[i] = (int64_t)per_cu * device_cu_count(f->device);
+        }
+        f->owner_block = fed_owner_threads(blocks, total, largest, places);
         if (D.workgroups_per_client <= 0) {
             // automatic: the sampling launch fills the GPU once
             int per_cu = 0;
