@@ -24,7 +24,8 @@ constexpr int lg_min_waves()
 }
 
 // WIDE: a model of 4 GiB or more, whose rows are found by 64-bit products.
-template <typename T, int D, int LANES, int VEC, bool SCATTER, bool WIDE>
+// GIVEN: the scatter of a sampled tensor whose values are given (lg_chunk).
+template <typename T, int D, int LANES, int VEC, bool SCATTER, bool WIDE, bool GIVEN>
 __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER, WIDE>())) k_loss_grad(const LGParams<T> P)
 {
     constexpr int DM = D > 0 ? D : kMaxModes;
@@ -83,7 +84,7 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER, WIDE>())) k
         const int64_t s_step = (int64_t)(tiled ? nwaves : nwaves * (int)gridDim.x) * B.chunk_samples;
         for (int64_t s0 = b0 + (int64_t)first * B.chunk_samples; s0 < b1; s0 += s_step) {
             const LGParams<T>& Q = params();
-            lg_chunk<T, D, LANES, VEC, SCATTER, WIDE>(Q, s0, Q.passes, lane, priv, bkey, by, bcnt, b0, tiled, scale,
+            lg_chunk<T, D, LANES, VEC, SCATTER, WIDE, GIVEN>(Q, s0, Q.passes, lane, priv, bkey, by, bcnt, b0, tiled, scale,
                                                 lacc, Q.sc.step);
         }
         const LGParams<T>& W = params();
@@ -92,7 +93,7 @@ __global__ void __launch_bounds__(1024, (lg_min_waves<T, D, SCATTER, WIDE>())) k
         if (!SCATTER || !tiled || j >= W.nblocks) break;
     }
 
-    if (P.loss_out) {
+    if (!GIVEN && P.loss_out) {
         for (int off = 32; off >= 1; off >>= 1) lacc += xor_shfl(lacc, off);
         if (P.loss_parts) {
             if (lane == 0) P.loss_parts[(int64_t)blockIdx.x * nwaves + wave] = lacc;
@@ -190,12 +191,19 @@ using BAKernel = void (*)(const LGParams<T>);
     X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(4, 2) X(8, 2) X(16, 2) X(32, 2) X(64, 2) X(2, 4) X(4, 4) X(8, 4) X(16, 4) X(32, 4) X(64, 4)
 #define GCP_LG_SHAPES_F64(X) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(4, 2) X(8, 2) X(16, 2) X(32, 2) X(64, 2) X(64, 4)
 
+// What a call's kernel does in its loop: no scatter (objective only, the sampled
+// tensor is written, or every mode is bucketed), or the scatter of some mode
+// (LDS-private or atomic), of drawn or listed samples or of given values.
+enum class LGForm { no_scatter, scatter, scatter_given };
+
 template <typename T, int D, bool WIDE>
-inline LGKernel<T> pick_shape(bool scatter, int lanes, int vec)
+inline LGKernel<T> pick_shape(LGForm form, int lanes, int vec)
 {
-#define GCP_CASE(LN, VC)        \
-    if (lanes == LN && vec == VC) \
-        return scatter ? k_loss_grad<T, D, LN, VC, true, WIDE> : k_loss_grad<T, D, LN, VC, false, WIDE>;
+#define GCP_CASE(LN, VC)                                                                        \
+    if (lanes == LN && vec == VC)                                                               \
+        return form == LGForm::scatter         ? k_loss_grad<T, D, LN, VC, true, WIDE, false>   \
+               : form == LGForm::scatter_given ? k_loss_grad<T, D, LN, VC, true, WIDE, true>    \
+                                               : k_loss_grad<T, D, LN, VC, false, WIDE, false>;
     if constexpr (sizeof(T) == 4) {
         GCP_LG_SHAPES_F32(GCP_CASE)
     } else {
@@ -220,19 +228,18 @@ inline BAKernel<T> pick_bucket_shape(int lanes, int vec)
 }
 
 // The kernels of order D (0: any order) at a lane shape, null when the shape
-// is not built.  scatter: the kernel that scatters in its loop (some mode is
-// LDS-private or atomic).  WIDE is built for orders 3 and 4 (order 0 has
-// 64-bit products anyway).
+// is not built.  WIDE is built for orders 3 and 4 (order 0 has 64-bit products
+// anyway).
 template <typename T, int D, bool WIDE>
-LGKernel<T> loss_grad_kernel(bool scatter, int lanes, int vec);
+LGKernel<T> loss_grad_kernel(LGForm form, int lanes, int vec);
 template <typename T, int D, bool WIDE>
 BAKernel<T> bucket_kernel(int lanes, int vec);
 
 #define GCP_LG_INSTANTIATE(T, D, WIDE)                                         \
     template <>                                                                \
-    LGKernel<T> loss_grad_kernel<T, D, WIDE>(bool scatter, int lanes, int vec) \
+    LGKernel<T> loss_grad_kernel<T, D, WIDE>(LGForm form, int lanes, int vec) \
     {                                                                          \
-        return pick_shape<T, D, WIDE>(scatter, lanes, vec);                    \
+        return pick_shape<T, D, WIDE>(form, lanes, vec);                    \
     }                                                                          \
     template <>                                                                \
     BAKernel<T> bucket_kernel<T, D, WIDE>(int lanes, int vec)                  \
@@ -242,7 +249,7 @@ BAKernel<T> bucket_kernel(int lanes, int vec);
 
 #define GCP_LG_DECLARE(T, D, WIDE)                                              \
     template <>                                                                 \
-    LGKernel<T> loss_grad_kernel<T, D, WIDE>(bool scatter, int lanes, int vec); \
+    LGKernel<T> loss_grad_kernel<T, D, WIDE>(LGForm form, int lanes, int vec); \
     template <>                                                                 \
     BAKernel<T> bucket_kernel<T, D, WIDE>(int lanes, int vec);
 

@@ -47,13 +47,13 @@ GCP_LG_DECLARE(double, 3, true)
 GCP_LG_DECLARE(double, 4, true)
 
 template <typename T>
-static LGKernel<T> pick_kernel(KernelOrder o, bool scatter, int lanes, int vec)
+static LGKernel<T> pick_kernel(KernelOrder o, LGForm form, int lanes, int vec)
 {
     switch (o.order) {
-    case 3: return o.wide ? loss_grad_kernel<T, 3, true>(scatter, lanes, vec) : loss_grad_kernel<T, 3, false>(scatter, lanes, vec);
-    case 4: return o.wide ? loss_grad_kernel<T, 4, true>(scatter, lanes, vec) : loss_grad_kernel<T, 4, false>(scatter, lanes, vec);
-    case 5: return loss_grad_kernel<T, 5, false>(scatter, lanes, vec);
-    default: return loss_grad_kernel<T, 0, false>(scatter, lanes, vec);
+    case 3: return o.wide ? loss_grad_kernel<T, 3, true>(form, lanes, vec) : loss_grad_kernel<T, 3, false>(form, lanes, vec);
+    case 4: return o.wide ? loss_grad_kernel<T, 4, true>(form, lanes, vec) : loss_grad_kernel<T, 4, false>(form, lanes, vec);
+    case 5: return loss_grad_kernel<T, 5, false>(form, lanes, vec);
+    default: return loss_grad_kernel<T, 0, false>(form, lanes, vec);
     }
 }
 
@@ -269,8 +269,10 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
         lanes = 32;
         vec = 2;
     }
-    const bool scatter = !loss_only && bucket_mask != all_modes;
-    LGKernel<T> kern = pick_kernel<T>(order, scatter, lanes, vec);
+    const LGForm form = loss_only || bucket_mask == all_modes ? LGForm::no_scatter
+                        : given_values                        ? LGForm::scatter_given
+                                                              : LGForm::scatter;
+    LGKernel<T> kern = pick_kernel<T>(order, form, lanes, vec);
     if (!kern) return set_error(GCP_ERR_UNSUPPORTED, "tile lanes = %d, vec = %d not built for this dtype", lanes, vec);
     const uintptr_t align = (uintptr_t)vec * sizeof(T);
     if (((uintptr_t)A % align) != 0) return set_error(GCP_ERR_ARG, "A is not %d-byte aligned", (int)align);
@@ -312,6 +314,12 @@ static gcp_status launch_loss_grad(const gcp_tensor_s* t, const gcp_sample_param
                                                             lds_bytes));
         if (per_cu < 1) return set_error(GCP_ERR_UNSUPPORTED, "kernel does not fit on a CU (LDS %zu B)", lds_bytes);
     }
+    // the kernels for given values need half the registers of those that draw,
+    // but twice the wavefronts only add into the same lines at once and flush
+    // twice the private copies (4e5 samples: 172x25000x300 at rank 6 in float 50.5
+    // us with 32 wavefronts per CU, 44.7 with 16; 1000x800x600x400 at rank 16 in
+    // double 181 and 171 us)
+    if (form == LGForm::scatter_given) per_cu = std::min(per_cu, std::max(1, 16 / nwaves));
     const int64_t resident = (int64_t)per_cu * cus;
     if (bucket_mask) {
         // with LDS-private modes no more workgroups than run at once: each adds
