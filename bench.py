@@ -530,11 +530,12 @@ def traffic_summary(dirs, tile: G.Tile) -> dict:
                                "write_size_kib": cw, "fetch_factor": ff, "write_factor": fw}
     per = {}
     total_r = total_w = 0.0
-    # the exact instantiations of the benchmark's call (0: nothing scattered in
-    # the sampling loop; the tile's lane shape)
+    # the exact instantiations of the benchmark's call (zeros: nothing scattered
+    # in the sampling loop, rows by 32-bit offsets, values not given; the tile's
+    # lane shape)
     shape = f"3, {tile.lanes}, {tile.vec}"
-    for name, match in (("k_loss_grad", f"k_loss_grad<float, {shape}, 0>"),
-                        ("k_bucket_accum", f"k_bucket_accum<float, {shape}>"), ("k_adam", "k_adam<float")):
+    for name, match in (("k_loss_grad", f"k_loss_grad<float, {shape}, 0, 0, 0>"),
+                        ("k_bucket_accum", f"k_bucket_accum<float, {shape}, 0>"), ("k_adam", "k_adam<float")):
         try:
             kf, nd = _median_counter(fetch, "FETCH_SIZE", match)
             kw, _ = _median_counter(write, "WRITE_SIZE", match)

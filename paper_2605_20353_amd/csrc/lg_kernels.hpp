@@ -13,10 +13,13 @@ namespace gcp {
 // Wavefronts per SIMD the register allocation aims at: 8 (64 VGPRs) for the
 // float kernels of orders 3 and 4 that scatter nothing in their loop and for
 // their owner pass, which fit them (68-76 unconstrained; four owner shapes
-// spill one or two), 6 (80 VGPRs) for those of order 5, where up to 14 registers
-// spill at 8 (five-way 400x300x200x100x50:
-// the objective of 2^18 samples at rank 32 23.1 us at 8, 19.2 at 6, 19.5 at 4;
-// 2^20 samples at rank 20, all modes bucketed, 256, 240 and 240 us).
+// spill one or two).  2^21 samples, 8 against 6 or 4: the objective of a
+// 10000x8000x6000 tensor at rank 32 75.1 and 77.0 us; a 5000x5000x500x1000 one
+// with every mode bucketed at rank 16 240 and 250, 32 262 and 257, 64 394 and
+// 398 us.  6 (80 VGPRs) for those of order 5, where up to 14 registers spill at
+// 8 (400x300x200x100x50: the objective of 2^18 samples at rank 32 23.1 us at 8,
+// 19.2 at 6, 19.5 at 4; 2^20 samples at rank 20, all modes bucketed, 256, 240
+// and 240 us).
 template <typename T, int D, bool SCATTER, bool WIDE>
 constexpr int lg_min_waves()
 {
