@@ -25,6 +25,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -502,8 +503,9 @@ def _counter_rows(d: str):
 
 
 def _flags_as_digits(name: str) -> str:
-    """A kernel's name with its bool template arguments as 0 and 1 (demanglers print either)."""
-    return name.replace("false", "0").replace("true", "1")
+    """A kernel's name with its bool template arguments as 0 and 1 (demanglers print either), less those
+    at its end that are 0."""
+    return re.sub(r"(, 0)+>", ">", name.replace("false", "0").replace("true", "1"))
 
 
 def _median_counter(rows, counter: str, kernel_sub: str) -> float:
@@ -530,12 +532,12 @@ def traffic_summary(dirs, tile: G.Tile) -> dict:
                                "write_size_kib": cw, "fetch_factor": ff, "write_factor": fw}
     per = {}
     total_r = total_w = 0.0
-    # the exact instantiations of the benchmark's call (zeros: nothing scattered
-    # in the sampling loop, rows by 32-bit offsets, values not given; the tile's
-    # lane shape)
+    # the exact instantiations of the benchmark's call (no flag set: nothing
+    # scattered in the sampling loop, rows by 32-bit offsets, values not given;
+    # the tile's lane shape)
     shape = f"3, {tile.lanes}, {tile.vec}"
-    for name, match in (("k_loss_grad", f"k_loss_grad<float, {shape}, 0, 0, 0>"),
-                        ("k_bucket_accum", f"k_bucket_accum<float, {shape}, 0>"), ("k_adam", "k_adam<float")):
+    for name, match in (("k_loss_grad", f"k_loss_grad<float, {shape}>"),
+                        ("k_bucket_accum", f"k_bucket_accum<float, {shape}>"), ("k_adam", "k_adam<float")):
         try:
             kf, nd = _median_counter(fetch, "FETCH_SIZE", match)
             kw, _ = _median_counter(write, "WRITE_SIZE", match)
